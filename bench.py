@@ -973,7 +973,7 @@ def main():
     torch.cuda.synchronize()
     T = time.perf_counter() - t0
     ws.profile(False)
-    ms_dir, n_dir, ms_res, n_res = ws.read_profile()
+    ms_iter, n_iter, _, _ = ws.read_profile()
     check = check_solve(grid, w, st.psi(), ws, opts)
 
     # achievable-bandwidth reference outside the timed region: a plain
@@ -993,13 +993,11 @@ def main():
     rhs = 3 * args.steps
     value = N * N * rhs / T
     F = 8 * N * N * n * n
-    # algorithmic bytes per direction-update launch, averaged over both
-    # parities (the live timing samples both alike): odd k reads r, p_{k-1}
-    # and writes p_k (3 fields); even k also reads p_{k-2} and x and writes
-    # x (6 fields)
-    alg_bytes = 4.5 * F
-    achieved = alg_bytes / (ms_dir * 1e-3) / 1e9
-    traffic = measured_traffic(F, tiles[0])
+    # algorithmic bytes per CG iteration launch, averaged over both parities
+    # (the live timing samples both alike): odd k reads r, p and writes r, p
+    # (4 fields); even k also reads p_{k-2} and x and writes x (7 fields)
+    alg_bytes = 5.5 * F
+    achieved = alg_bytes / (ms_iter * 1e-3) / 1e9
     srt = sorted(stage_ms)
 
     def pct(q):
@@ -1033,17 +1031,16 @@ def main():
         "all_converged": all_conv,
         "check_solve": check,
         "roofline": {
-            "kernel": ("k_cg_dir (CG direction update: p = r + b p, <p, A p>; x += the "
-                       "last two a p every other launch)"),
+            "kernel": ("k_cg_step (one CG iteration: r -= a A p, p = r + b p, the sums "
+                       "of the next a and b; x += the last two a p every other launch)"),
             "bound": "hbm",
             "achieved": achieved,
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
-            "traffic": traffic,
-            "avg_launch_ms": ms_dir,
-            "samples": n_dir,
-            "residual_kernel_avg_ms": ms_res,
+            "traffic": None,
+            "avg_launch_ms": ms_iter,
+            "samples": n_iter,
             "algorithmic_bytes_per_launch": alg_bytes,
             "copy_GBps": copy_gbs,
             "frac_of_copy": achieved / copy_gbs,

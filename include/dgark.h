@@ -219,13 +219,14 @@ int  dg_workspace_held_bytes(const dg_workspace* ws, size_t* bytes);
 int  dg_workspace_create(const dg_grid* grid, int mode, dg_workspace** out);
 void dg_workspace_destroy(dg_workspace* ws);         /* NULL-safe */
 
-/* Measurement support.  While enabled, every CG polling chunk of a solve on
- * this workspace times one direction-update kernel launch and one
- * residual-update kernel launch with HIP events recorded by those dispatches
- * on the solve's stream (only iterations the device really executed are
- * counted).  dg_profile_read
- * stores {sum_ms_direction, launches, sum_ms_residual, launches} accumulated
- * since the previous read and resets them.  Host-only bookkeeping. */
+/* Measurement support.  While enabled, every polling chunk of a plain FP64
+ * solve on this workspace times one launch of the CG iteration kernel with HIP
+ * events recorded by that dispatch on the solve's stream (only iterations the
+ * device really executed are counted; launches with and without the update of
+ * x alternate).  dg_profile_read stores {sum_ms_iteration, launches, 0, 0}
+ * (the last two: the residual update, which is part of the iteration kernel)
+ * accumulated since the previous read and resets them.  Host-only
+ * bookkeeping. */
 int  dg_profile_enable(dg_workspace* ws, int on);
 int  dg_profile_read(dg_workspace* ws, double* out4);
 

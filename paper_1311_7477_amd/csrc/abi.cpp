@@ -130,9 +130,10 @@ size_t ws_bytes(const dg_grid* g, int mode) {
     const size_t L = l64_elems(g->geom);
     int blocks = stencil_blocks(g->geom);
     if (blocks < pointwise_block_cap()) blocks = pointwise_block_cap();
-    size_t b = 4 * L * sizeof(double) + 2 * F;          // x, r, p0, p1; s1, s2
+    size_t b = 6 * L * sizeof(double);                  // x, r, p0, p1; s1, s2
     b += (size_t)blocks * 4 * sizeof(double);           // partials
-    b += sizeof(CgScalars) + kCntBytes + 4 * sizeof(double);
+    b += step_part_bytes(g->geom);
+    b += 2 * sizeof(CgScalars) + kCntBytes + 4 * sizeof(double);
     if (prec_of(mode) == DG_PREC_MIXED) b += 3 * L * sizeof(float);
     if (mode & DG_WS_FD)
         b += L * sizeof(double) + F + 3 * sizeof(CgScalars) + fd_bytes(g);   // z, wbak, sc3
@@ -151,62 +152,43 @@ int read_scalars(dg_workspace* ws, const CgScalars* dev, CgScalars* host,
     return DG_OK;
 }
 
-// Queue CG iterations in chunks and poll the device `done` flag one chunk
-// behind, so the device never waits for the host.  Iterations queued after
-// convergence exit at their first instruction.
 // Fold the sampled kernel durations of a completed poll slot into the
 // workspace totals; a sample counts only if the device really executed that
 // iteration (iterations queued after convergence exit immediately).
 int harvest_profile(dg_workspace* ws, int slot, int device_iter) {
     if (ws->pev_iter[slot] < 0) return DG_OK;
-    if (device_iter > ws->pev_iter[slot]) {
-        float a = 0.f, b = 0.f;
+    if (device_iter >= ws->pev_iter[slot]) {
+        float a = 0.f;
         HIP_TRY(hipEventElapsedTime(&a, ws->pev[slot][0], ws->pev[slot][1]));
-        HIP_TRY(hipEventElapsedTime(&b, ws->pev[slot][2], ws->pev[slot][3]));
         ws->prof_ms[0] += a;
-        ws->prof_ms[1] += b;
         ws->prof_n[0] += 1;
-        ws->prof_n[1] += 1;
     }
     ws->pev_iter[slot] = -1;
     return DG_OK;
 }
 
-template <class T>
-int cg_loop(const Geom& geom, const OpConst<double>& k, T* x, T* r, T* p0, T* p1,
-            CgScalars* sc, int max_iter, int check_every, dg_workspace* ws,
-            hipStream_t s, CgScalars* final_host) {
-    const int chunk = check_every > 0 ? check_every : 32;
+// Queue launches in chunks of `chunk` and poll the device `done` flag one
+// chunk behind, so the device never waits for the host; launches queued after
+// the solve has stopped do nothing.  queue(i, slot) queues launch i of at most
+// `total`, whose sampled events (if any) belong to poll slot `slot`.
+template <class Queue>
+int cg_loop(int total, int chunk, const CgScalars* sc, dg_workspace* ws, hipStream_t s,
+            CgScalars* final_host, Queue&& queue) {
     int issued = 0, round = 0, prev = -1;
     ws->pev_iter[0] = ws->pev_iter[1] = -1;
     for (;;) {
-        int m = max_iter - issued;
+        int m = total - issued;
         if (m > chunk) m = chunk;
         const int slot = round & 1;
-        // the sampled iteration alternates between the first and the second
-        // of a chunk, so that FP64 solves time direction updates with and
-        // without the x update alike
-        const int ti = (round & 1) && m > 1 ? 1 : 0;
         for (int i = 0; i < m; ++i) {
-            hipError_t e;
-            if (ws->prof_on && i == ti) {
-                e = launch_cg_dir_timed<T>(geom, k, x, r, p0, p1, sc, ws->d, s,
-                                           ws->pev[slot][0], ws->pev[slot][1]);
-                if (e != hipSuccess) return hip_fail(e, "cg direction launch");
-                e = launch_cg_res_timed<T>(geom, k, r, p0, p1, sc, ws->d, s,
-                                           ws->pev[slot][2], ws->pev[slot][3]);
-                if (e != hipSuccess) return hip_fail(e, "cg residual launch");
-                ws->pev_iter[slot] = issued + i;
-            } else {
-                e = launch_cg_iter<T>(geom, k, x, r, p0, p1, sc, ws->d, s);
-                if (e != hipSuccess) return hip_fail(e, "cg iteration launch");
-            }
+            const int rc = queue(issued + i, i, slot);
+            if (rc != DG_OK) return rc;
         }
         issued += m;
         HIP_TRY(hipMemcpyAsync(&ws->host[slot], sc, sizeof(CgScalars),
                                hipMemcpyDeviceToHost, s));
         HIP_TRY(hipEventRecord(ws->ev[slot], s));
-        if (issued >= max_iter) {
+        if (issued >= total) {
             HIP_TRY(hipEventSynchronize(ws->ev[slot]));
             *final_host = ws->host[slot];
             if (prev >= 0) {
@@ -231,6 +213,45 @@ int cg_loop(const Geom& geom, const OpConst<double>& k, T* x, T* r, T* p0, T* p1
     }
 }
 
+// The plain FP64 CG of a periodic grid, one launch per iteration.  A launch
+// evaluates the residual of the one before it, so the launch after the last
+// iteration allowed finds the solve stopped: max_iter + 2 launches, rounded up
+// to an even count (after which sc[0] is the newest).
+int cg_steps(const dg_grid* g, const double* omega, const dg_cg_opts& o, dg_workspace* ws,
+             hipStream_t s, CgScalars* fin) {
+    // the second residual takes the RK field that does not hold the input
+    StepBuffers v{ws->x, ws->r, omega == ws->s1 ? ws->s2 : ws->s1, ws->p0, ws->p1,
+                  {ws->d.sc, ws->d.sc + 1}, ws->step_part, ws->step_max_blocks};
+    const int chunk = o.check_every > 0 ? (o.check_every + (o.check_every & 1)) : 32;
+    const int most = o.max_iter < (1 << 30) ? o.max_iter : (1 << 30);
+    const int total = (most + 3) & ~1;
+    int round = -1;
+    return cg_loop(total, chunk, ws->d.sc, ws, s, fin, [&](int launch, int i, int slot) {
+        // the sampled launch alternates between the first and the second of a
+        // chunk, so that launches with and without the x update count alike
+        if (i == 0) ++round;
+        const bool timed = ws->prof_on && i == (round & 1);
+        hipError_t e = launch_cg_step(g->geom, g->k64, launch & 1, v, ws->d.counters, s,
+                                      timed ? ws->pev[slot][0] : nullptr,
+                                      timed ? ws->pev[slot][1] : nullptr);
+        if (e != hipSuccess) return hip_fail(e, "cg iteration launch");
+        if (timed) ws->pev_iter[slot] = launch;
+        return (int)DG_OK;
+    });
+}
+
+// The plain FP64 CG with a Dirichlet axis: direction and residual kernels.
+int cg_pairs(const dg_grid* g, const dg_cg_opts& o, dg_workspace* ws, hipStream_t s,
+             CgScalars* fin) {
+    if (ws->prof_on) return hip_fail(hipErrorInvalidValue, "cg direction launch");
+    return cg_loop(o.max_iter, o.check_every > 0 ? o.check_every : 32, ws->d.sc, ws, s, fin,
+                   [&](int, int, int) {
+        hipError_t e = launch_cg_iter<double>(g->geom, g->k64, ws->x, ws->r, ws->p0, ws->p1,
+                                              ws->d.sc, ws->d, s);
+        return e == hipSuccess ? (int)DG_OK : hip_fail(e, "cg iteration launch");
+    });
+}
+
 // FP64 CG from the guess ca*pa + cb*pb into x (x must not alias pa or pb).
 int cg_fp64(const dg_grid* g, const double* omega, double* x, const double* pa,
             double ca, const double* pb, double cb, const dg_cg_opts& o,
@@ -242,8 +263,8 @@ int cg_fp64(const dg_grid* g, const double* omega, double* x, const double* pa,
     e = launch_cg_init(g->geom, g->k64, omega, pa, pb, ca, cb, ws->x, ws->r, ws->d, s);
     if (e != hipSuccess) return hip_fail(e, "cg init launch");
     CgScalars fin;
-    int rc = cg_loop<double>(g->geom, g->k64, ws->x, ws->r, ws->p0, ws->p1, ws->d.sc,
-                             o.max_iter, o.check_every, ws, s, &fin);
+    int rc = g->geom.bcx || g->geom.bcy ? cg_pairs(g, o, ws, s, &fin)
+                                        : cg_steps(g, omega, o, ws, s, &fin);
     if (rc != DG_OK) return rc;
     e = launch_cg_finish<double>(g->geom, g->k64, ws->x, ws->p0, ws->p1, x, g->area,
                                  ws->d, s);
@@ -579,7 +600,7 @@ void dg_workspace_destroy(dg_workspace* ws) {
     (void)hipSetDevice(ws->device);
     void* bufs[] = {ws->x, ws->r, ws->p0, ws->p1, ws->s1, ws->s2, ws->r32,
                     ws->q0, ws->q1, ws->z, ws->wbak, ws->sc3, ws->d.sc, ws->d.counters,
-                    ws->d.partials, ws->d.out3};
+                    ws->d.partials, ws->d.out3, ws->step_part};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
     fd_destroy(ws->fd);
@@ -611,6 +632,7 @@ int dg_workspace_create(const dg_grid* g, int mode, dg_workspace** out) {
     int blocks = stencil_blocks(g->geom);
     if (blocks < pointwise_block_cap()) blocks = pointwise_block_cap();
     ws->d.max_blocks = blocks;
+    ws->step_max_blocks = step_max_blocks(g->geom);
     auto alloc = [&](void** p, size_t b) -> bool {
         return hipMalloc(p, b) == hipSuccess;
     };
@@ -619,8 +641,10 @@ int dg_workspace_create(const dg_grid* g, int mode, dg_workspace** out) {
               alloc((void**)&ws->r, L * sizeof(double)) &&
               alloc((void**)&ws->p0, L * sizeof(double)) &&
               alloc((void**)&ws->p1, L * sizeof(double)) &&
-              alloc((void**)&ws->s1, F) && alloc((void**)&ws->s2, F) &&
-              alloc((void**)&ws->d.sc, sizeof(CgScalars)) &&
+              alloc((void**)&ws->s1, L * sizeof(double)) &&
+              alloc((void**)&ws->s2, L * sizeof(double)) &&
+              alloc((void**)&ws->d.sc, 2 * sizeof(CgScalars)) &&
+              alloc((void**)&ws->step_part, step_part_bytes(g->geom)) &&
               alloc((void**)&ws->d.counters, kCntBytes) &&
               alloc((void**)&ws->d.partials, (size_t)blocks * 4 * sizeof(double)) &&
               alloc((void**)&ws->d.out3, 4 * sizeof(double));
@@ -659,7 +683,7 @@ int dg_workspace_create(const dg_grid* g, int mode, dg_workspace** out) {
     ws->pev_iter[0] = ws->pev_iter[1] = -1;
     // counters must start at zero (each reduction resets its own)
     e = hipMemset(ws->d.counters, 0, kCntBytes);
-    if (e == hipSuccess) e = hipMemset(ws->d.sc, 0, sizeof(CgScalars));
+    if (e == hipSuccess) e = hipMemset(ws->d.sc, 0, 2 * sizeof(CgScalars));
     if (e == hipSuccess && ws->sc3) e = hipMemset(ws->sc3, 0, 3 * sizeof(CgScalars));
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) { dg_workspace_destroy(ws); return hip_fail(e, "workspace init"); }

@@ -25,13 +25,17 @@ struct dg_workspace {
     int n, nx, ny, mode, device;
     size_t elems;
     double *x, *r, *p0, *p1;   // CG vectors, lane-interleaved layout
-    double *s1, *s2;           // RK stage fields, canonical layout
+    double *s1, *s2;           // RK stage fields, canonical layout; the plain CG keeps its
+                               // second residual in the one that does not hold its input
+                               // (both sized for an L64 vector)
     float *r32, *q0, *q1;      // mixed precision: FP32 residual and directions
     double* z;                 // preconditioned residual (DG_WS_FD workspaces)
     double* wbak;              // DG_WS_FD: omega at the start of a queued RK step
     CgScalars* sc3;            // DG_WS_FD: device scalars of the three queued stage solves
     dgk::FdDevice* fd;         // fast-diagonalisation preconditioner, or NULL
     DevScratch d;
+    double* step_part;         // block sums of the one-kernel CG iteration, two parities
+    int step_max_blocks;
     CgScalars* host;           // pinned, 4 slots (2 poll slots + 2 spare)
     hipEvent_t ev[2];
     hipEvent_t tev[4];

@@ -5,6 +5,7 @@
 // and device CG scalars, and its arithmetic is that of dg_rk_step.
 #include <hip/hip_runtime.h>
 
+#include <bitset>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -18,29 +19,30 @@ using namespace dgk;
 
 namespace {
 
-enum ListKind { kCell = 0, kRow, kPwRows, kPwCells, kPwElems, kListCount };
+enum ListKind { kCell = 0, kStep, kRow, kPwRows, kPwCells, kPwElems, kListCount };
 
-// Launch groups: one per (polynomial order, cell tile height, bracket tile
-// height); every kernel kind of a group is one fused launch.
+// Launch groups: one per (polynomial order, cell tile height, CG tile height,
+// bracket tile height); every kernel kind of a group is one fused launch.
 constexpr int kCellShapes[3] = {4, 8, 16};
 constexpr int kRowShapes[2] = {8, 16};
-constexpr int kShapes = 6;
+constexpr int kShapes = 18;
 constexpr int kGroups = kMaxN * kShapes;
-static_assert(kGroups <= 32, "group_mask holds one bit per launch group");
+using GroupMask = std::bitset<kGroups>;
+
+int cell_shape(int waves) { return waves == 4 ? 0 : (waves == 8 ? 1 : 2); }
 
 int group_of(const Geom& g) {
-    const int ci = g.cw == 4 ? 0 : (g.cw == 8 ? 1 : 2);
     const int ri = g.rw == 8 ? 0 : 1;
-    return (g.n - 1) * kShapes + ci * 2 + ri;
+    return (g.n - 1) * kShapes + (cell_shape(g.cw) * 3 + cell_shape(step_waves(g))) * 2 + ri;
 }
 
 struct GroupShape {
-    int n, cw, rw;
+    int n, cw, sw, rw;
 };
 
 GroupShape shape_of(int gi) {
     const int n = gi / kShapes + 1, s = gi % kShapes;
-    return GroupShape{n, kCellShapes[s / 2], kRowShapes[s % 2]};
+    return GroupShape{n, kCellShapes[s / 6], kCellShapes[s / 2 % 3], kRowShapes[s % 2]};
 }
 
 struct Slot {
@@ -67,13 +69,14 @@ struct dg_batch {
     std::vector<Slot> slots;
     BatchInst* d_inst = nullptr;   // device records
     BatchInst* h_inst = nullptr;   // pinned host records
-    CgScalars* d_sc = nullptr;     // device CG scalars, one per slot
+    CgScalars* d_sc = nullptr;     // device CG scalars, one per slot, and (second half)
+                                   // those of the odd CG launches
     CgScalars* h_sc = nullptr;     // pinned: 3 x capacity (2 poll slots + final)
     int* d_counts = nullptr;       // device item counts [n-1][kind]
     int* h_counts = nullptr;       // pinned
     DevList lists[kGroups][kListCount];
     bool lists_dirty = true;
-    unsigned group_mask = 0;       // bit gi set if some slot is in launch group gi
+    GroupMask group_mask;          // bit gi set if some slot is in launch group gi
     hipEvent_t ev[2] = {nullptr, nullptr};
     hipStream_t cap = nullptr;     // capture stream
     bool use_graphs = true;
@@ -107,15 +110,15 @@ int grid_of(const dg_batch* b, int gi, int kind) {
 // upload them.
 int rebuild_lists(dg_batch* b, hipStream_t s) {
     std::vector<BatchItem> h[kGroups][kListCount];
-    unsigned mask = 0;
+    GroupMask mask;
     for (int i = 0; i < b->capacity; ++i) {
         const Slot& sl = b->slots[i];
         if (!sl.used) continue;
         const BatchInst& r = b->h_inst[i];
         const int gi = group_of(r.g);
-        mask |= 1u << gi;
-        const int counts[kListCount] = {r.cell_nblocks, r.row_nblocks, r.nb_rows,
-                                        r.nb_cells, r.nb_elems};
+        mask.set(gi);
+        const int counts[kListCount] = {r.cell_nblocks, r.step_nblocks, r.row_nblocks,
+                                        r.nb_rows, r.nb_cells, r.nb_elems};
         for (int k = 0; k < kListCount; ++k)
             for (int q = 0; q < counts[k]; ++q) h[gi][k].push_back(BatchItem{i, q});
     }
@@ -157,12 +160,12 @@ int rebuild_lists(dg_batch* b, hipStream_t s) {
 
 int enqueue_setup(dg_batch* b, hipStream_t s) {
     for (int gi = 0; gi < kGroups; ++gi) {
-        if (!(b->group_mask & (1u << gi))) continue;
+        if (!b->group_mask[gi]) continue;
         const GroupShape q = shape_of(gi);
-        hipError_t e = launch_batch(q.n, q.cw, q.rw, BatchKernel::Mean, b->d_inst,
+        hipError_t e = launch_batch(q.n, q.cw, q.sw, q.rw, BatchKernel::Mean, b->d_inst,
                                     list_of(b, gi, kPwRows), grid_of(b, gi, kPwRows), s);
         if (e == hipSuccess)
-            e = launch_batch(q.n, q.cw, q.rw, BatchKernel::Init, b->d_inst,
+            e = launch_batch(q.n, q.cw, q.sw, q.rw, BatchKernel::Init, b->d_inst,
                              list_of(b, gi, kCell), grid_of(b, gi, kCell), s);
         if (e != hipSuccess) return hip_fail(e, "batch setup launch");
     }
@@ -175,11 +178,9 @@ int enqueue_setup(dg_batch* b, hipStream_t s) {
 int enqueue_chunk(dg_batch* b, int gi, hipStream_t s) {
     const GroupShape q = shape_of(gi);
     for (int i = 0; i < b->chunk; ++i) {
-        hipError_t e = launch_batch(q.n, q.cw, q.rw, BatchKernel::Dir, b->d_inst,
-                                    list_of(b, gi, kCell), grid_of(b, gi, kCell), s);
-        if (e == hipSuccess)
-            e = launch_batch(q.n, q.cw, q.rw, BatchKernel::Res, b->d_inst,
-                             list_of(b, gi, kCell), grid_of(b, gi, kCell), s);
+        hipError_t e = launch_batch(q.n, q.cw, q.sw, q.rw,
+                                    i & 1 ? BatchKernel::StepOdd : BatchKernel::StepEven,
+                                    b->d_inst, list_of(b, gi, kStep), grid_of(b, gi, kStep), s);
         if (e != hipSuccess) return hip_fail(e, "batch CG launch");
     }
     return DG_OK;
@@ -187,15 +188,15 @@ int enqueue_chunk(dg_batch* b, int gi, hipStream_t s) {
 
 int enqueue_finish(dg_batch* b, hipStream_t s) {
     for (int gi = 0; gi < kGroups; ++gi) {
-        if (!(b->group_mask & (1u << gi))) continue;
+        if (!b->group_mask[gi]) continue;
         const GroupShape q = shape_of(gi);
-        hipError_t e = launch_batch(q.n, q.cw, q.rw, BatchKernel::Finish, b->d_inst,
+        hipError_t e = launch_batch(q.n, q.cw, q.sw, q.rw, BatchKernel::Finish, b->d_inst,
                                     list_of(b, gi, kPwCells), grid_of(b, gi, kPwCells), s);
         if (e == hipSuccess)
-            e = launch_batch(q.n, q.cw, q.rw, BatchKernel::SubMean, b->d_inst,
+            e = launch_batch(q.n, q.cw, q.sw, q.rw, BatchKernel::SubMean, b->d_inst,
                              list_of(b, gi, kPwElems), grid_of(b, gi, kPwElems), s);
         if (e == hipSuccess)
-            e = launch_batch(q.n, q.cw, q.rw, BatchKernel::Rhs, b->d_inst,
+            e = launch_batch(q.n, q.cw, q.sw, q.rw, BatchKernel::Rhs, b->d_inst,
                              list_of(b, gi, kRow), grid_of(b, gi, kRow), s);
         if (e != hipSuccess) return hip_fail(e, "batch finish launch");
     }
@@ -221,7 +222,7 @@ int ensure_graphs(dg_batch* b) {
     destroy_graphs(b);
     int rc = capture(b, [b](hipStream_t s) { return enqueue_setup(b, s); }, &b->g_setup);
     for (int gi = 0; gi < kGroups && rc == DG_OK; ++gi)
-        if (b->group_mask & (1u << gi))
+        if (b->group_mask[gi])
             rc = capture(b, [b, gi](hipStream_t s) { return enqueue_chunk(b, gi, s); },
                          &b->g_chunk[gi]);
     if (rc == DG_OK)
@@ -241,10 +242,10 @@ int run(dg_batch* b, int (*fn)(dg_batch*, hipStream_t), hipGraphExec_t g, hipStr
 
 // Launch groups with a member whose solve is still running (h: polled
 // scalars).
-unsigned running_groups(const dg_batch* b, const CgScalars* h) {
-    unsigned m = 0;
+GroupMask running_groups(const dg_batch* b, const CgScalars* h) {
+    GroupMask m;
     for (int i = 0; i < b->capacity; ++i)
-        if (b->slots[i].used && !h[i].done) m |= 1u << group_of(b->h_inst[i].g);
+        if (b->slots[i].used && !h[i].done) m.set(group_of(b->h_inst[i].g));
     return m;
 }
 
@@ -263,7 +264,7 @@ int dg_batch_create(int capacity, dg_batch** out) {
     bool ok = hipGetDevice(&b->device) == hipSuccess &&
               hipMalloc((void**)&b->d_inst, capacity * sizeof(BatchInst)) == hipSuccess &&
               hipHostMalloc((void**)&b->h_inst, capacity * sizeof(BatchInst)) == hipSuccess &&
-              hipMalloc((void**)&b->d_sc, capacity * sizeof(CgScalars)) == hipSuccess &&
+              hipMalloc((void**)&b->d_sc, 2 * capacity * sizeof(CgScalars)) == hipSuccess &&
               hipHostMalloc((void**)&b->h_sc, 3 * capacity * sizeof(CgScalars)) == hipSuccess &&
               hipMalloc((void**)&b->d_counts, kGroups * kListCount * sizeof(int)) == hipSuccess &&
               hipHostMalloc((void**)&b->h_counts, kGroups * kListCount * sizeof(int)) == hipSuccess &&
@@ -273,7 +274,7 @@ int dg_batch_create(int capacity, dg_batch** out) {
     if (ok) {
         std::memset(b->h_inst, 0, capacity * sizeof(BatchInst));
         std::memset(b->h_counts, 0, kGroups * kListCount * sizeof(int));
-        ok = hipMemset(b->d_sc, 0, capacity * sizeof(CgScalars)) == hipSuccess &&
+        ok = hipMemset(b->d_sc, 0, 2 * capacity * sizeof(CgScalars)) == hipSuccess &&
              hipMemset(b->d_counts, 0, kGroups * kListCount * sizeof(int)) == hipSuccess &&
              hipDeviceSynchronize() == hipSuccess;
     }
@@ -344,6 +345,9 @@ int dg_batch_attach(dg_batch* b, const dg_grid* g, double* omega, double dt,
     r.p0 = sl.ws->p0;
     r.p1 = sl.ws->p1;
     r.sc = b->d_sc + i;
+    r.sc1 = b->d_sc + b->capacity + i;
+    r.step_part = sl.ws->step_part;
+    r.step_max_blocks = sl.ws->step_max_blocks;
     r.counters = sl.ws->d.counters;
     r.partials = sl.ws->d.partials;
     b->lists_dirty = true;
@@ -459,6 +463,7 @@ int dg_batch_rk_step(dg_batch* b, const dg_cg_opts* opts, int* iters_out,
             double* win[3] = {sl.omega, sl.ws->s1, sl.ws->s2};
             double* wout[3] = {sl.ws->s1, sl.ws->s2, sl.omega};
             r.w_in = win[k];
+            r.r1 = win[k] == sl.ws->s1 ? sl.ws->s2 : sl.ws->s1;
             r.w_out = wout[k];
             r.w_n = k ? sl.omega : nullptr;
             r.ra = RhsArgs{1.0, 1.0, 1.0, 1.0 / 3.0, sl.D, sl.dt, ra_a[k], ra_b[k], 0};
@@ -472,10 +477,10 @@ int dg_batch_rk_step(dg_batch* b, const dg_cg_opts* opts, int* iters_out,
         // CG chunks, polled one chunk behind; a group drops out once all its
         // members were seen done
         int issued = 0, round = 0, prev = -1;
-        unsigned live = b->group_mask;
+        GroupMask live = b->group_mask;
         for (;;) {
             for (int gi = 0; gi < kGroups; ++gi) {
-                if (!(live & (1u << gi))) continue;
+                if (!live[gi]) continue;
                 if (b->use_graphs) {
                     HIP_TRY(hipGraphLaunch(b->g_chunk[gi], s));
                 } else {
@@ -496,7 +501,7 @@ int dg_batch_rk_step(dg_batch* b, const dg_cg_opts* opts, int* iters_out,
             if (prev >= 0) {
                 HIP_TRY(hipEventSynchronize(b->ev[prev]));
                 live &= running_groups(b, b->h_sc + prev * b->capacity);
-                if (!live) break;
+                if (live.none()) break;
             }
             prev = slot;
             ++round;

@@ -21,7 +21,7 @@ struct ItemList {
 // the stage part is rewritten by the host before every RK stage.
 struct BatchInst {
     Geom g;
-    int cell_tilesX, cell_nblocks, row_tilesX, row_nblocks;
+    int cell_tilesX, cell_nblocks, row_tilesX, row_nblocks, step_tilesX, step_nblocks;
     int nb_rows, nb_cells, nb_elems;
     long rows, cells, elems;
     double area, tol2;
@@ -37,18 +37,21 @@ struct BatchInst {
     double* psi;           // solve output (canonical)
     RhsArgs ra;
     // workspace
-    double *x, *r, *p0, *p1;
+    double *x, *r, *r1, *p0, *p1;   // r1: stage part (the free RK field)
     CgScalars* sc;
+    CgScalars* sc1;          // scalars of odd CG launches
+    double* step_part;       // block sums of the CG launches, two parities
+    int step_max_blocks;
     unsigned* counters;
     double* partials;
 };
 
-enum class BatchKernel { Mean, Init, Dir, Res, Finish, SubMean, Rhs };
+enum class BatchKernel { Mean, Init, StepEven, StepOdd, Finish, SubMean, Rhs };
 
 void fill_batch_geometry(BatchInst& b);
 // One fused launch of `kind` for polynomial order n with cell tiles of
-// cw waves (Init, Dir, Res) and bracket tiles of rw waves (Rhs).
-hipError_t launch_batch(int n, int cw, int rw, BatchKernel kind, const BatchInst* inst,
+// cw waves (Init) or sw waves (Step*: one CG iteration of that parity) and bracket tiles of rw waves (Rhs).
+hipError_t launch_batch(int n, int cw, int sw, int rw, BatchKernel kind, const BatchInst* inst,
                         const ItemList& list, int grid, hipStream_t s);
 
 }  // namespace dgk

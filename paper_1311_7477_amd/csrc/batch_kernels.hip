@@ -11,7 +11,7 @@
 // captured graph serves every stage.
 #include "batch.h"
 #include "dg_launch.h"
-#include "cg_body.h"
+#include "cg_step_body.h"
 #include "pw_body.h"
 #include "rhs_body.h"
 
@@ -47,22 +47,17 @@ __global__ __launch_bounds__(64 * WV, (N <= 4 ? 4 : 1)) void kb_cg_init(const Ba
     }
 }
 
-template <int N, int WV>
-__global__ __launch_bounds__(64 * WV, (N <= 4 ? 4 : 1)) void kb_cg_dir(const BatchInst* __restrict__ inst, ItemList list) {
-    __shared__ YFaces<N, double, WV> lds;
+template <int N, int WV, int PAR>
+__global__ __launch_bounds__(64 * WV, (N <= 4 ? 4 : 1)) void kb_cg_step(const BatchInst* __restrict__ inst, ItemList list) {
+    __shared__ StepLds<N, WV> lds;
     DG_FOR_ITEMS(list) {
-        cg_dir_body<N, double, WV>(item_.b, B.g, B.cell_tilesX, B.cell_nblocks, B.k,
-                               B.r, B.p0, B.p1, B.x, B.sc, B.counters + kCntDir * kCntStride, B.partials, lds);
-    }
-}
-
-template <int N, int WV>
-__global__ __launch_bounds__(64 * WV, (N <= 4 ? 4 : 1)) void kb_cg_res(const BatchInst* __restrict__ inst, ItemList list) {
-    __shared__ YFaces<N, double, WV> lds;
-    DG_FOR_ITEMS(list) {
-        cg_res_body<N, double, WV>(item_.b, B.g, B.cell_tilesX, B.cell_nblocks, B.k,
-                               B.p0, B.p1, B.r, B.sc,
-                               B.counters + kCntRes * kCntStride, B.partials, lds);
+        const size_t stride = step_part_stride(B.step_max_blocks);
+        cg_step_body<N, WV, false>(item_.b, B.g, B.step_tilesX, B.step_nblocks, B.k, PAR,
+                                   PAR ? B.r1 : B.r, PAR ? B.r : B.r1, PAR ? B.p1 : B.p0,
+                                   PAR ? B.p0 : B.p1, B.x, PAR ? B.sc1 : B.sc,
+                                   PAR ? B.sc : B.sc1, B.step_part + PAR * stride,
+                                   B.step_part + (1 - PAR) * stride,
+                                   B.counters + kCntDir * kCntStride, lds);
     }
 }
 
@@ -101,6 +96,9 @@ void fill_batch_geometry(BatchInst& b) {
     CellLaunch cl(g);
     b.cell_tilesX = cl.tilesX;
     b.cell_nblocks = cl.nblocks;
+    const StepLaunch sl(g, step_waves(g));
+    b.step_tilesX = sl.tilesX;
+    b.step_nblocks = sl.nblocks;
     RowLaunch rl(g);
     b.row_tilesX = rl.tilesX;
     b.row_nblocks = rl.nblocks;
@@ -112,7 +110,7 @@ void fill_batch_geometry(BatchInst& b) {
     b.nb_elems = pw_blocks(b.elems, pointwise_block_cap());
 }
 
-hipError_t launch_batch(int n, int cw, int rw, BatchKernel kind, const BatchInst* inst,
+hipError_t launch_batch(int n, int cw, int sw, int rw, BatchKernel kind, const BatchInst* inst,
                         const ItemList& list, int grid, hipStream_t s) {
     const dim3 pw(kPwThreads);
     switch (kind) {
@@ -123,12 +121,12 @@ hipError_t launch_batch(int n, int cw, int rw, BatchKernel kind, const BatchInst
             DG_DISPATCH_NW(n, cw, hipLaunchKernelGGL((kb_cg_init<NN, WW>), dim3(grid),
                                                      dim3(64 * WW), 0, s, inst, list));
             break;
-        case BatchKernel::Dir:
-            DG_DISPATCH_NW(n, cw, hipLaunchKernelGGL((kb_cg_dir<NN, WW>), dim3(grid),
+        case BatchKernel::StepEven:
+            DG_DISPATCH_NW(n, sw, hipLaunchKernelGGL((kb_cg_step<NN, WW, 0>), dim3(grid),
                                                      dim3(64 * WW), 0, s, inst, list));
             break;
-        case BatchKernel::Res:
-            DG_DISPATCH_NW(n, cw, hipLaunchKernelGGL((kb_cg_res<NN, WW>), dim3(grid),
+        case BatchKernel::StepOdd:
+            DG_DISPATCH_NW(n, sw, hipLaunchKernelGGL((kb_cg_step<NN, WW, 1>), dim3(grid),
                                                      dim3(64 * WW), 0, s, inst, list));
             break;
         case BatchKernel::Finish:

@@ -54,15 +54,24 @@ hipError_t launch_cg_dir(const Geom& g, const OpConst<double>& k, double* x, S* 
 template <class S>
 hipError_t launch_cg_res(const Geom& g, const OpConst<double>& k, S* r, S* p0, S* p1,
                          CgScalars* sc, const DevScratch& d, hipStream_t s);
-// Timed variants: start / stop events record the dispatch's own timestamps.
-template <class S>
-hipError_t launch_cg_dir_timed(const Geom& g, const OpConst<double>& k, double* x, S* r,
-                               S* p0, S* p1, CgScalars* sc, const DevScratch& d,
-                               hipStream_t s, hipEvent_t start, hipEvent_t stop);
-template <class S>
-hipError_t launch_cg_res_timed(const Geom& g, const OpConst<double>& k, S* r, S* p0, S* p1,
-                               CgScalars* sc, const DevScratch& d, hipStream_t s,
-                               hipEvent_t start, hipEvent_t stop);
+// The one-kernel iteration of the plain FP64 solve on a periodic grid
+// (cg_step_kernels.hip): the launch of parity par (0, 1, 0, ... from the setup
+// on) reads sc[par] and the block sums of that parity and writes the other
+// ones, so after an even number of launches sc[0] is the newest.  r0: the
+// setup's residual; r1: a second residual buffer.  start / stop, if not null,
+// record the dispatch's own timestamps.
+struct StepBuffers {
+    double *x, *r0, *r1, *p0, *p1;
+    CgScalars* sc[2];
+    double* part;       // 2 step_part_stride(max_blocks) doubles
+    int max_blocks;     // step_max_blocks
+};
+int step_waves(const Geom& g);         // waves (cell rows) per tile
+int step_max_blocks(const Geom& g);    // the most blocks any tile shape launches
+size_t step_part_bytes(const Geom& g);
+hipError_t launch_cg_step(const Geom& g, const OpConst<double>& k, int par, const StepBuffers& v,
+                          unsigned* counters, hipStream_t s, hipEvent_t start = nullptr,
+                          hipEvent_t stop = nullptr);
 template <class S>
 hipError_t launch_cg_iter(const Geom& g, const OpConst<double>& k, double* x, S* r,
                           S* p0, S* p1, CgScalars* sc, const DevScratch& d,

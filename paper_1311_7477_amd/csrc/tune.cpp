@@ -21,7 +21,7 @@ constexpr int kRowCandidates[2] = {8, 16};
 bool valid_cw(int cw) { return cw == 4 || cw == 8 || cw == 16; }
 bool valid_rw(int rw) { return rw == 8 || rw == 16; }
 
-// Mean milliseconds of one CG iteration (direction + residual kernels) with
+// Mean milliseconds of one CG iteration with
 // the grid's current cell tile, from a fresh CG setup on omega that cannot
 // converge (tol = 0).  Returns a negative status on error.
 int time_cg(dg_grid* g, const double* omega, dg_workspace* ws, int reps, hipEvent_t e0,
@@ -32,19 +32,20 @@ int time_cg(dg_grid* g, const double* omega, dg_workspace* ws, int reps, hipEven
     if (e == hipSuccess)
         e = launch_cg_init(geom, g->k64, omega, nullptr, nullptr, 0.0, 0.0, ws->x, ws->r,
                            ws->d, s);
-    for (int i = 0; e == hipSuccess && i < 2; ++i)
-        e = launch_cg_iter<double>(geom, g->k64, ws->x, ws->r, ws->p0, ws->p1, ws->d.sc,
-                                   ws->d, s);
+    const StepBuffers v{ws->x, ws->r, ws->s1, ws->p0, ws->p1, {ws->d.sc, ws->d.sc + 1},
+                        ws->step_part, ws->step_max_blocks};
+    int par = 0;
+    for (int i = 0; e == hipSuccess && i < 2; ++i, par ^= 1)
+        e = launch_cg_step(geom, g->k64, par, v, ws->d.counters, s);
     if (e == hipSuccess) e = hipEventRecord(e0, s);
-    for (int i = 0; e == hipSuccess && i < reps; ++i)
-        e = launch_cg_iter<double>(geom, g->k64, ws->x, ws->r, ws->p0, ws->p1, ws->d.sc,
-                                   ws->d, s);
+    for (int i = 0; e == hipSuccess && i < reps; ++i, par ^= 1)
+        e = launch_cg_step(geom, g->k64, par, v, ws->d.counters, s);
     if (e == hipSuccess) e = hipEventRecord(e1, s);
     if (e == hipSuccess) e = hipEventSynchronize(e1);
     if (e == hipSuccess) e = hipEventElapsedTime(ms, e0, e1);
     if (e != hipSuccess) return hip_fail(e, "tuning CG launch");
     CgScalars h;
-    HIP_TRY(hipMemcpy(&h, ws->d.sc, sizeof h, hipMemcpyDeviceToHost));
+    HIP_TRY(hipMemcpy(&h, ws->d.sc + par, sizeof h, hipMemcpyDeviceToHost));
     if (h.done)
         return fail(DG_E_INVAL, "tuning needs an omega whose mean-free part is nonzero "
                     "(the CG stopped after %d iterations)", h.iter);

@@ -249,7 +249,7 @@ class Workspace:
         _check(lib().dg_profile_enable(self._h, 1 if on else 0))
 
     def read_profile(self):
-        """(mean ms direction kernel, samples, mean ms residual kernel, samples)"""
+        """(mean ms of the CG iteration kernel, samples, nan, 0)"""
         out = (ctypes.c_double * 4)()
         _check(lib().dg_profile_read(self._h, out))
         a, na, b, nb = out
