@@ -29,6 +29,9 @@ constexpr int kShapes = 18;
 constexpr int kGroups = kMaxN * kShapes;
 using GroupMask = std::bitset<kGroups>;
 
+// streams for the CG chunks (the hardware queues of a process by default)
+constexpr int kMaxLanes = 4;
+
 int cell_shape(int waves) { return waves == 4 ? 0 : (waves == 8 ? 1 : 2); }
 
 int group_of(const Geom& g) {
@@ -71,13 +74,19 @@ struct dg_batch {
     BatchInst* h_inst = nullptr;   // pinned host records
     CgScalars* d_sc = nullptr;     // device CG scalars, one per slot, and (second half)
                                    // those of the odd CG launches
-    CgScalars* h_sc = nullptr;     // pinned: 3 x capacity (2 poll slots + final)
+    CgScalars* h_sc = nullptr;     // pinned: capacity (final), then 2 x kMaxLanes x
+                                   // capacity (poll slots of the group streams)
     int* d_counts = nullptr;       // device item counts [n-1][kind]
     int* h_counts = nullptr;       // pinned
     DevList lists[kGroups][kListCount];
     bool lists_dirty = true;
     GroupMask group_mask;          // bit gi set if some slot is in launch group gi
-    hipEvent_t ev[2] = {nullptr, nullptr};
+    // CG chunks of different launch groups run on streams of their own (group
+    // gi of a step takes lane rank(gi) mod kMaxLanes): groups share nothing, and
+    // the iterations of a small group leave most of the chip idle
+    hipStream_t lane[kMaxLanes] = {};
+    hipEvent_t ev[kMaxLanes][2] = {};
+    hipEvent_t fork = nullptr;
     hipStream_t cap = nullptr;     // capture stream
     bool use_graphs = true;
     bool graphs_valid = false;
@@ -249,6 +258,69 @@ GroupMask running_groups(const dg_batch* b, const CgScalars* h) {
     return m;
 }
 
+// Queue the CG chunks of every launch group until all its members are done,
+// each group on a stream (lane) of its own that starts when the setup queued on
+// s has run; s goes on when every lane has.  A lane is polled one chunk behind,
+// and its groups drop out once all their members were seen done.  On an error
+// the lanes are waited for (they use the members' buffers).
+int run_chunks(dg_batch* b, const dg_cg_opts& o, hipStream_t s) {
+    GroupMask of_lane[kMaxLanes];
+    int lanes = 0;
+    for (int gi = 0; gi < kGroups; ++gi)
+        if (b->group_mask[gi]) of_lane[lanes++ % kMaxLanes].set(gi);
+    if (lanes > kMaxLanes) lanes = kMaxLanes;
+    auto body = [&]() -> int {
+        HIP_TRY(hipEventRecord(b->fork, s));
+        GroupMask live[kMaxLanes];
+        for (int l = 0; l < lanes; ++l) {
+            HIP_TRY(hipStreamWaitEvent(b->lane[l], b->fork, 0));
+            live[l] = of_lane[l];
+        }
+        int issued = 0;
+        for (int round = 0;; ++round) {
+            const int slot = round & 1;
+            bool any = false;
+            for (int l = 0; l < lanes; ++l) {
+                if (live[l].none()) continue;
+                any = true;
+                for (int gi = 0; gi < kGroups; ++gi) {
+                    if (!live[l][gi]) continue;
+                    if (b->use_graphs) {
+                        HIP_TRY(hipGraphLaunch(b->g_chunk[gi], b->lane[l]));
+                    } else {
+                        const int rc = enqueue_chunk(b, gi, b->lane[l]);
+                        if (rc != DG_OK) return rc;
+                    }
+                }
+                CgScalars* h = b->h_sc + (size_t)(1 + 2 * l + slot) * b->capacity;
+                HIP_TRY(hipMemcpyAsync(h, b->d_sc, b->capacity * sizeof(CgScalars),
+                                       hipMemcpyDeviceToHost, b->lane[l]));
+                HIP_TRY(hipEventRecord(b->ev[l][slot], b->lane[l]));
+            }
+            if (!any) break;
+            issued += b->chunk;
+            if (issued >= o.max_iter + b->chunk) break;
+            if (round == 0) continue;
+            for (int l = 0; l < lanes; ++l) {
+                if (live[l].none()) continue;
+                HIP_TRY(hipEventSynchronize(b->ev[l][1 - slot]));
+                live[l] &= running_groups(
+                    b, b->h_sc + (size_t)(1 + 2 * l + 1 - slot) * b->capacity);
+            }
+        }
+        // s waits for the lanes' last chunks
+        for (int l = 0; l < lanes; ++l) {
+            HIP_TRY(hipEventRecord(b->ev[l][0], b->lane[l]));
+            HIP_TRY(hipStreamWaitEvent(s, b->ev[l][0], 0));
+        }
+        return DG_OK;
+    };
+    const int rc = body();
+    if (rc != DG_OK)
+        for (int l = 0; l < lanes; ++l) (void)hipStreamSynchronize(b->lane[l]);
+    return rc;
+}
+
 }  // namespace
 
 extern "C" {
@@ -265,12 +337,16 @@ int dg_batch_create(int capacity, dg_batch** out) {
               hipMalloc((void**)&b->d_inst, capacity * sizeof(BatchInst)) == hipSuccess &&
               hipHostMalloc((void**)&b->h_inst, capacity * sizeof(BatchInst)) == hipSuccess &&
               hipMalloc((void**)&b->d_sc, 2 * capacity * sizeof(CgScalars)) == hipSuccess &&
-              hipHostMalloc((void**)&b->h_sc, 3 * capacity * sizeof(CgScalars)) == hipSuccess &&
+              hipHostMalloc((void**)&b->h_sc, (1 + 2 * kMaxLanes) * capacity * sizeof(CgScalars)) ==
+                  hipSuccess &&
               hipMalloc((void**)&b->d_counts, kGroups * kListCount * sizeof(int)) == hipSuccess &&
               hipHostMalloc((void**)&b->h_counts, kGroups * kListCount * sizeof(int)) == hipSuccess &&
-              hipEventCreateWithFlags(&b->ev[0], hipEventDisableTiming) == hipSuccess &&
-              hipEventCreateWithFlags(&b->ev[1], hipEventDisableTiming) == hipSuccess &&
+              hipEventCreateWithFlags(&b->fork, hipEventDisableTiming) == hipSuccess &&
               hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking) == hipSuccess;
+    for (int l = 0; ok && l < kMaxLanes; ++l)
+        ok = hipStreamCreateWithFlags(&b->lane[l], hipStreamNonBlocking) == hipSuccess &&
+             hipEventCreateWithFlags(&b->ev[l][0], hipEventDisableTiming) == hipSuccess &&
+             hipEventCreateWithFlags(&b->ev[l][1], hipEventDisableTiming) == hipSuccess;
     if (ok) {
         std::memset(b->h_inst, 0, capacity * sizeof(BatchInst));
         std::memset(b->h_counts, 0, kGroups * kListCount * sizeof(int));
@@ -304,7 +380,10 @@ void dg_batch_destroy(dg_batch* b) {
     if (b->h_sc) (void)hipHostFree(b->h_sc);
     if (b->d_counts) (void)hipFree(b->d_counts);
     if (b->h_counts) (void)hipHostFree(b->h_counts);
-    for (hipEvent_t e : b->ev) if (e) (void)hipEventDestroy(e);
+    for (auto& pair : b->ev)
+        for (hipEvent_t e : pair) if (e) (void)hipEventDestroy(e);
+    if (b->fork) (void)hipEventDestroy(b->fork);
+    for (hipStream_t l : b->lane) if (l) (void)hipStreamDestroy(l);
     if (b->cap) (void)hipStreamDestroy(b->cap);
     delete b;
 }
@@ -474,41 +553,11 @@ int dg_batch_rk_step(dg_batch* b, const dg_cg_opts* opts, int* iters_out,
                                hipMemcpyHostToDevice, s));
         int rc = run(b, enqueue_setup, b->g_setup, s);
         if (rc != DG_OK) return rc;
-        // CG chunks, polled one chunk behind; a group drops out once all its
-        // members were seen done
-        int issued = 0, round = 0, prev = -1;
-        GroupMask live = b->group_mask;
-        for (;;) {
-            for (int gi = 0; gi < kGroups; ++gi) {
-                if (!live[gi]) continue;
-                if (b->use_graphs) {
-                    HIP_TRY(hipGraphLaunch(b->g_chunk[gi], s));
-                } else {
-                    rc = enqueue_chunk(b, gi, s);
-                    if (rc != DG_OK) return rc;
-                }
-            }
-            issued += b->chunk;
-            const int slot = round & 1;
-            HIP_TRY(hipMemcpyAsync(b->h_sc + slot * b->capacity, b->d_sc,
-                                   b->capacity * sizeof(CgScalars),
-                                   hipMemcpyDeviceToHost, s));
-            HIP_TRY(hipEventRecord(b->ev[slot], s));
-            if (issued >= o.max_iter + b->chunk) {
-                HIP_TRY(hipEventSynchronize(b->ev[slot]));
-                break;
-            }
-            if (prev >= 0) {
-                HIP_TRY(hipEventSynchronize(b->ev[prev]));
-                live &= running_groups(b, b->h_sc + prev * b->capacity);
-                if (live.none()) break;
-            }
-            prev = slot;
-            ++round;
-        }
+        rc = run_chunks(b, o, s);
+        if (rc != DG_OK) return rc;
         rc = run(b, enqueue_finish, b->g_finish, s);
         if (rc != DG_OK) return rc;
-        CgScalars* fin = b->h_sc + 2 * b->capacity;
+        CgScalars* fin = b->h_sc;
         HIP_TRY(hipMemcpyAsync(fin, b->d_sc, b->capacity * sizeof(CgScalars),
                                hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
