@@ -260,7 +260,7 @@ int cg_fp64(const dg_grid* g, const double* omega, double* x, const double* pa,
     hipError_t e = launch_cg_mean(g->geom, g->k64, omega, pa, pb, ca, cb, g->area,
                                   tol2, o.max_iter, ws->d, s);
     if (e != hipSuccess) return hip_fail(e, "cg mean launch");
-    e = launch_cg_init(g->geom, g->k64, omega, pa, pb, ca, cb, ws->x, ws->r, ws->d, s);
+    e = launch_cg_init(g->geom, g->k64, omega, pa, pb, ca, cb, g->area, ws->x, ws->r, ws->d, s);
     if (e != hipSuccess) return hip_fail(e, "cg init launch");
     CgScalars fin;
     int rc = g->geom.bcx || g->geom.bcy ? cg_pairs(g, o, ws, s, &fin)
@@ -300,7 +300,7 @@ int cg_mixed(const dg_grid* g, const double* omega, double* x, const double* pa,
     hipError_t e = launch_cg_mean(g->geom, g->k64, omega, pa, pb, ca, cb, g->area,
                                   tol2, o.max_iter, ws->d, s);
     if (e != hipSuccess) return hip_fail(e, "cg mean launch");
-    e = launch_cg_init(g->geom, g->k64, omega, pa, pb, ca, cb, ws->x, ws->r, ws->d, s);
+    e = launch_cg_init(g->geom, g->k64, omega, pa, pb, ca, cb, g->area, ws->x, ws->r, ws->d, s);
     if (e != hipSuccess) return hip_fail(e, "cg init launch");
     int rc = read_scalars(ws, ws->d.sc, &ws->host[2], s);
     if (rc != DG_OK) return rc;
@@ -345,7 +345,8 @@ int cg_mixed(const dg_grid* g, const double* omega, double* x, const double* pa,
 }
 
 // z = M r on node planes in the precision T, then z and <r, z>_W in FP64
-// (device scalars in d.sc).
+// (device scalars in d.sc).  The first z is the first direction and goes where
+// the direction kernel would store it (iteration 0 writes p1).
 template <class T>
 int precond_step(const dg_grid* g, dg_workspace* ws, const DevScratch& d, hipStream_t s) {
     T* planes = reinterpret_cast<T*>(ws->fd->img0);
@@ -359,8 +360,10 @@ int precond_step(const dg_grid* g, dg_workspace* ws, const DevScratch& d, hipStr
     int rc = fd_apply_image(ws->fd, sizeof(T) == sizeof(float), s);
     if (rc != DG_OK) return rc;
     e = layout == kFdFolded
-            ? launch_from_planes_fold<T>(g->geom, g->k64, planes, Kx, ws->z, ws->r, &d, s)
-            : launch_from_image_dot<T>(g->geom, g->k64, planes, dense, ws->z, ws->r, d, s);
+            ? launch_from_planes_fold<T>(g->geom, g->k64, planes, Kx, ws->z, ws->p1, ws->r,
+                                         g->area, &d, s)
+            : launch_from_image_dot<T>(g->geom, g->k64, planes, dense, ws->z, ws->p1, ws->r,
+                                       g->area, d, s);
     if (e != hipSuccess) return hip_fail(e, "image conversion launch");
     return DG_OK;
 }
@@ -384,7 +387,7 @@ int pcg_queue(const dg_grid* g, const double* omega, const double* pa, double ca
     hipError_t e = launch_cg_mean(g->geom, g->k64, omega, pa, pb, ca, cb, g->area, tol2,
                                   o.max_iter, d, s);
     if (e != hipSuccess) return hip_fail(e, "cg mean launch");
-    e = launch_cg_init(g->geom, g->k64, omega, pa, pb, ca, cb, ws->x, ws->r, d, s);
+    e = launch_cg_init(g->geom, g->k64, omega, pa, pb, ca, cb, g->area, ws->x, ws->r, d, s);
     if (e != hipSuccess) return hip_fail(e, "cg init launch");
     for (int it = 0; it < iters; ++it) {
         int rc = pcg_iteration(g, fp32, d, ws, s);
@@ -441,8 +444,7 @@ int cg_pcg(const dg_grid* g, const double* omega, double* x, const double* pa,
         if (rc != DG_OK) return rc;
         h = ws->host[2];
     }
-    hipError_t e = launch_cg_finish<double>(g->geom, g->k64, ws->x, ws->p0, ws->p1, x, g->area,
-                                            ws->d, s);
+    hipError_t e = launch_pcg_finish(g->geom, g->k64, ws->x, ws->p0, ws->p1, x, ws->d, s);
     if (e != hipSuccess) return hip_fail(e, "cg finish launch");
     HIP_TRY(hipStreamSynchronize(s));
     return pcg_result(h, st);
@@ -797,7 +799,7 @@ int dg_precond_apply(const dg_grid* g, const double* r, double* z, dg_workspace*
     if (rc != DG_OK) return rc;
     e = layout == kFdFolded
             ? launch_from_planes_fold<double>(g->geom, g->k64, ws->fd->img0, Kx, z, nullptr,
-                                              nullptr, s)
+                                              nullptr, g->area, nullptr, s)
             : launch_from_image<double>(g->geom, g->k64, ws->fd->img0, dense, z, s);
     if (e != hipSuccess) return hip_fail(e, "image conversion launch");
     return DG_OK;
@@ -881,8 +883,7 @@ int rk_step_queued(const dg_grid* g, double* omega, dg_state* st, const dg_step_
         d.sc = ws->sc3 + k;
         int rc = pcg_queue(g, win[k], pa, ca, pb, cb, opts->cg, false, 1, d, ws, s);
         if (rc != DG_OK) return rc;
-        hipError_t e = launch_cg_finish<double>(g->geom, g->k64, ws->x, ws->p0, ws->p1, x,
-                                                g->area, d, s);
+        hipError_t e = launch_pcg_finish(g->geom, g->k64, ws->x, ws->p0, ws->p1, x, d, s);
         if (e != hipSuccess) return hip_fail(e, "cg finish launch");
         state_push(st, fr, ts[k]);
         RhsParams p{fc[0], fc[1], fc[2], fc[3], opts->D, dt, ra[k], rb[k], 0};

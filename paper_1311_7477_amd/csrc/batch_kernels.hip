@@ -42,7 +42,7 @@ __global__ __launch_bounds__(64 * WV, (N <= 4 ? 4 : 1)) void kb_cg_init(const Ba
     __shared__ YFaces<N, double, WV> lds;
     DG_FOR_ITEMS(list) {
         cg_init_body<N, WV>(item_.b, B.g, B.cell_tilesX, B.cell_nblocks, B.k, B.w_in,
-                        B.pa, B.pb, B.ca, B.cb, B.x, B.r, B.sc,
+                        B.pa, B.pb, B.ca, B.cb, 1.0 / B.area, B.x, B.r, B.sc,
                         B.counters + kCntInit * kCntStride, B.partials, lds);
     }
 }
@@ -64,9 +64,10 @@ __global__ __launch_bounds__(64 * WV, (N <= 4 ? 4 : 1)) void kb_cg_step(const Ba
 template <int N>
 __global__ __launch_bounds__(kPwThreads) void kb_cg_finish(const BatchInst* __restrict__ inst,
                                                            ItemList list) {
+    __shared__ FinishLds<N> lds;
     DG_FOR_ITEMS(list) {
-        cg_finish_body<N>(item_.b, B.nb_cells, B.g, B.k, B.x, B.p0, B.p1, B.psi,
-                          B.area, B.sc, B.counters + kCntFinish * kCntStride, B.partials);
+        cg_finish_body<N, double, false>(item_.b, B.nb_cells, B.g, B.k, B.x, B.p0, B.p1, B.psi,
+                          B.area, B.sc, B.counters + kCntFinish * kCntStride, B.partials, lds);
     }
 }
 

@@ -24,7 +24,10 @@
 // of a solve.
 #pragma once
 
+#include <type_traits>
+
 #include "dg_device.h"
+#include "dg_stage.h"
 
 namespace dgk {
 
@@ -42,6 +45,10 @@ struct CellCtx {
     // homogeneous Dirichlet axes: first / second / last cell along x and y
     bool lo_x, sec_x, hi_x, lo_y, sec_y, hi_y;
     CellRef self, r, l, u, d;
+    // the wave's row of the tile: its cells are the lanes below `count`, its
+    // first cell and those of the rows above and below (canonical offsets)
+    int count;
+    long row0, rowU, rowD;
 };
 
 template <int N>
@@ -51,6 +58,8 @@ __device__ __forceinline__ CellRef cell_ref(const Geom& g, int G, int cx, int cy
     c.l64 = ((long)cy * G + (cx >> 6)) * (N * N * 64) + (cx & 63);
     return c;
 }
+
+__device__ __forceinline__ int cya_row(int cy, int ny) { return cy < ny ? cy : 0; }
 
 template <int N, int WV>
 __device__ __forceinline__ CellCtx make_cell_ctx(const Geom& g, int tilesX,
@@ -84,6 +93,10 @@ __device__ __forceinline__ CellCtx make_cell_ctx(const Geom& g, int tilesX,
     c.l = cell_ref<N>(g, G, cxl, cya);
     c.u = cell_ref<N>(g, G, cxa, cyu);
     c.d = cell_ref<N>(g, G, cxa, cyd);
+    c.count = cy < g.ny ? (g.nx - tx * 64 < 64 ? g.nx - tx * 64 : 64) : 0;
+    c.row0 = ((long)cya_row(cy, g.ny) * g.nx + tx * 64) * (N * N);
+    c.rowU = ((long)(cy + 1 < g.ny ? cy + 1 : 0) * g.nx + tx * 64) * (N * N);
+    c.rowD = ((long)(cy > 0 && cy < g.ny ? cy - 1 : g.ny - 1) * g.nx + tx * 64) * (N * N);
     return c;
 }
 
@@ -160,11 +173,49 @@ __device__ __forceinline__ T ydot(const T (&u)[N * N], int i, const T* w) {
     return s;
 }
 
+template <int N, class T>
+__device__ __forceinline__ void zero_cell(T (&u)[N * N]) {
+#pragma unroll
+    for (int e = 0; e < N * N; ++e) u[e] = 0;
+}
+
 // LDS for the y face scalars of one tile: [wave][face][i][lane]
 template <int N, class T, int WV>
 struct YFaces {
-    T v[WV * 2 * N * 64];
+    static constexpr int kWave = 2 * N * 64;      // values between waves
+    T v[WV * kWave];
+    __device__ T* row(int wave) { return v + wave * kWave; }
 };
+
+// The same with the wave's part large enough to stage a canonical row of cells
+// (before the face scalars are published, and again after a barrier past
+// their last use).
+template <int N, int WV>
+struct StagedFaces {
+    static constexpr int kWave = Stage<N>::SIZE > 2 * N * 64 ? Stage<N>::SIZE : 2 * N * 64;
+    alignas(16) double v[WV * kWave];
+    __device__ double* row(int wave) { return v + wave * kWave; }
+};
+
+// Whether the Laplacian stages canonical rows: from n = 3 on; below, a cell is
+// at most 32 contiguous bytes and lanes reading their own are as fast (n = 2,
+// 512^2: 11.2 us, staged 12.1).
+constexpr bool staged_rows(int n) { return n >= 3; }
+
+// Waves of the Laplacian on a grid with cell tiles of cw waves: at n = 5 only
+// one block of 8 waves fits a CU, whose loads, operator and stores then follow
+// one another; two blocks of 4 overlap them.
+__host__ __device__ constexpr int laplace_waves(int n, int cw) { return n == 5 ? 4 : cw; }
+
+// The values of the row of cells above / below the tile, in the lanes' order:
+// sources that read canonical fields stage the whole row, the others load each
+// lane's cell.
+template <int N, class T, class Src>
+__device__ __forceinline__ void halo_row(const Src& src, const CellCtx& c, bool up, double* buf,
+                                         T (&h)[N * N]) {
+    if constexpr (Src::kStaged) src.row(up ? c.rowU : c.rowD, c.count, buf, c.lane, h);
+    else if (c.active) src(up ? c.u : c.d, h);
+}
 
 // Lap_h u for this lane's cell.  `src(ref, out)` evaluates the field on a
 // halo cell; the own cell's values are passed in u.  Every thread of the
@@ -175,10 +226,10 @@ struct YFaces {
 // ISO: square cells and the same boundary kind on both axes, whose x and y
 // blocks coincide -- the y operator reads the x tables (half the constants
 // held in registers).
-template <int N, int WV, bool DIR = false, bool ISO = false, class T, class Src>
+template <int N, int WV, bool DIR = false, bool ISO = false, class T, class Src, class Lds>
 __device__ __forceinline__ void lap_cell(const CellCtx& c, const OpConst<T>& k,
                                          const Src& src, const T (&u)[N * N],
-                                         YFaces<N, T, WV>& lds, T (&out)[N * N]) {
+                                         Lds& lds, T (&out)[N * N]) {
     // The Dirichlet tables of the first cells (L0B, eRB, lLB) are chosen by
     // per-lane conditions.  Selecting a table pointer per lane would make
     // the compiler hold a per-lane copy of the selected constants; instead
@@ -190,15 +241,18 @@ __device__ __forceinline__ void lap_cell(const CellCtx& c, const OpConst<T>& k,
     T hR[N], hL[N], hU[N], hD[N];
 #pragma unroll
     for (int m = 0; m < N; ++m) hR[m] = hL[m] = hU[m] = hD[m] = 0;
-    if (c.active && !c.yin_u) {
+    T* mine = lds.row(c.wave) + c.lane;      // [lR, lL][i] at i * 64
+    if (c.count && !c.yin_u) {               // wave-uniform
         T h[N * N];
-        src(c.u, h);
+        zero_cell<N>(h);
+        halo_row<N>(src, c, true, (double*)lds.row(c.wave), h);
 #pragma unroll
         for (int i = 0; i < N; ++i) hU[i] = ydot<N>(h, i, k.lR);
     }
-    if (c.active && !c.yin_d) {
+    if (c.count && !c.yin_d) {
         T h[N * N];
-        src(c.d, h);
+        zero_cell<N>(h);
+        halo_row<N>(src, c, false, (double*)lds.row(c.wave), h);
         if (DIR && c.sec_y) {
 #pragma unroll
             for (int i = 0; i < N; ++i) hD[i] = ydot<N>(h, i, lLBy);
@@ -235,8 +289,8 @@ __device__ __forceinline__ void lap_cell(const CellCtx& c, const OpConst<T>& k,
         }
 #pragma unroll
         for (int i = 0; i < N; ++i) {
-            lds.v[((c.wave * 2 + 0) * N + i) * 64 + c.lane] = ydot<N>(u, i, k.lR);
-            lds.v[((c.wave * 2 + 1) * N + i) * 64 + c.lane] = dn[i];
+            mine[i * 64] = ydot<N>(u, i, k.lR);
+            mine[(N + i) * 64] = dn[i];
         }
     }
     // x face scalars from the neighbouring lanes
@@ -265,8 +319,8 @@ __device__ __forceinline__ void lap_cell(const CellCtx& c, const OpConst<T>& k,
     T fU[N], fD[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        fU[i] = c.yin_u ? lds.v[(((c.wave + 1) * 2 + 0) * N + i) * 64 + c.lane] : hU[i];
-        fD[i] = c.yin_d ? lds.v[(((c.wave - 1) * 2 + 1) * N + i) * 64 + c.lane] : hD[i];
+        fU[i] = c.yin_u ? mine[Lds::kWave + i * 64] : hU[i];
+        fD[i] = c.yin_d ? mine[-Lds::kWave + (N + i) * 64] : hD[i];
         if (DIR) {
             if (c.hi_y) fU[i] = 0;
             if (c.lo_y) fD[i] = 0;
@@ -318,14 +372,33 @@ __device__ __forceinline__ double wdot_cell(const OpConst<T>& k, const T (&a)[N 
     return s * k.wq;
 }
 
+// <a, 1>_W over one cell
+template <int N>
+__device__ __forceinline__ double wsum_cell(const OpConst<double>& k, const double (&a)[N * N]) {
+    double s = 0.0;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        double r = 0.0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) r = fmx(k.w[i], a[j * N + i], r);
+        s = fmx(r, k.w[j], s);
+    }
+    return s * k.wq;
+}
+
 template <int N, class T>
 struct SrcCanon {                       // u = f (canonical layout)
+    static constexpr bool kStaged = staged_rows(N);
     const T* f;
     __device__ void operator()(const CellRef& c, T (&u)[N * N]) const { ld_canon<N>(f, c, u); }
+    __device__ void row(long o, int count, double* buf, int lane, T (&u)[N * N]) const {
+        stage_in<N>(f + o, count, buf, lane, u);
+    }
 };
 
 template <int N, class S>
 struct SrcL64 {                         // u = f (L64 layout, stored as S)
+    static constexpr bool kStaged = false;
     const S* f;
     __device__ void operator()(const CellRef& c, double (&u)[N * N]) const {
         ld_l64<N>(f, c, u);
@@ -342,6 +415,7 @@ constexpr bool kStoredLow = sizeof(S) < sizeof(double);
 
 template <int N, class S>
 struct SrcDirection {                   // p = r (first) or cr r + beta p_old, L64
+    static constexpr bool kStaged = false;
     const S* r;
     const S* p;
     double beta, cr;
@@ -362,6 +436,7 @@ struct SrcDirection {                   // p = r (first) or cr r + beta p_old, L
 
 template <int N>
 struct SrcGuess {                       // x0 = ca pa + cb pb, canonical
+    static constexpr bool kStaged = false;
     const double* pa;
     const double* pb;
     double ca, cb;
@@ -383,35 +458,43 @@ struct SrcGuess {                       // x0 = ca pa + cb pb, canonical
     }
 };
 
-template <int N, class T>
-__device__ __forceinline__ void zero_cell(T (&u)[N * N]) {
-#pragma unroll
-    for (int e = 0; e < N * N; ++e) u[e] = 0;
-}
+// out = Lap_h u (canonical layout in and out).  Bound by memory: rows staged
+// through LDS against lanes loading and storing their own cells, n = 3,
+// 1153 x 701 36.9 -> 31.0 us; n = 4, 512^2 22.1 -> 16.0; n = 5, 2048^2 488 ->
+// 325 us (5.2 TB/s, a plain copy's rate).
+template <int N, int WV>
+using LaplaceLds = std::conditional_t<staged_rows(N), StagedFaces<N, WV>, YFaces<N, double, WV>>;
 
-// out = Lap_h u (canonical layout in and out)
 template <int N, int WV, bool DIR = false, bool ISO = false>
 __device__ __forceinline__ void laplace_body(
     int b, Geom g, int tilesX, int nblocks, const OpConst<double>& k,
     const double* __restrict__ u, double* __restrict__ out,
-    YFaces<N, double, WV>& lds) {
+    LaplaceLds<N, WV>& lds) {
     const CellCtx c = make_cell_ctx<N, WV>(g, tilesX, nblocks, b);
     SrcCanon<N, double> src{u};
     double v[N * N], lap[N * N];
-    if (c.active) src(c.self, v);
-    else zero_cell<N>(v);
-    lap_cell<N, WV, DIR, ISO>(c, k, src, v, lds, lap);
-    if (c.active) st_canon<N>(out, c.self, lap);
+    if constexpr (staged_rows(N)) {
+        src.row(c.row0, c.count, lds.row(c.wave), c.lane, v);
+        lap_cell<N, WV, DIR, ISO>(c, k, src, v, lds, lap);
+        __syncthreads();      // the face scalars are read: the buffers are free
+        stage_out<N>(out + c.row0, c.count, lds.row(c.wave), c.lane, lap);
+    } else {
+        if (c.active) src(c.self, v);
+        else zero_cell<N>(v);
+        lap_cell<N, WV, DIR, ISO>(c, k, src, v, lds, lap);
+        if (c.active) st_canon<N>(out, c.self, lap);
+    }
 }
 
 // CG setup (stencil part): x0 = guess (to L64; its mean is left in, see
 // cg_mean_body);
-// r0 = (omega - mean(omega)) + Lap_h x0 (to L64); partials <r0,r0>_W, <b,b>_W.
+// r0 = (omega - mean(omega)) + Lap_h x0 (to L64); partials <r0,r0>_W, <b,b>_W,
+// <x0,1>_W (inv_area: 1 / area, 0 with a Dirichlet axis).
 template <int N, int WV, bool DIR = false, bool ISO = false>
 __device__ __forceinline__ void cg_init_body(
     int b, Geom g, int tilesX, int nblocks, const OpConst<double>& k,
     const double* __restrict__ omega, const double* __restrict__ pa,
-    const double* __restrict__ pb, double ca, double cb,
+    const double* __restrict__ pb, double ca, double cb, double inv_area,
     double* __restrict__ x, double* __restrict__ r, CgScalars* sc,
     unsigned* counter, double* partials,
     YFaces<N, double, WV>& lds) {
@@ -422,23 +505,25 @@ __device__ __forceinline__ void cg_init_body(
     if (c.active) src(c.self, x0);
     else zero_cell<N>(x0);
     lap_cell<N, WV, DIR, ISO>(c, k, src, x0, lds, lap);
-    double part[2] = {0.0, 0.0};
+    double part[3] = {0.0, 0.0, 0.0};
     if (c.active) {
-        double b[N * N];
-        ld_canon<N>(omega, c.self, b);
+        double bv[N * N];
+        ld_canon<N>(omega, c.self, bv);
 #pragma unroll
         for (int e = 0; e < N * N; ++e) {
-            b[e] -= mo;
-            lap[e] += b[e];          // r0
+            bv[e] -= mo;
+            lap[e] += bv[e];          // r0
         }
         st_l64<N>(x, c.self, x0);
         st_l64<N>(r, c.self, lap);
         part[0] = wdot_cell<N>(k, lap, lap);
-        part[1] = wdot_cell<N>(k, b, b);
+        part[1] = wdot_cell<N>(k, bv, bv);
+        part[2] = wsum_cell<N>(k, x0);
     }
-    double tot[2];
-    if (reduce_last<2, 64 * WV>(part, partials, counter, nblocks, b, tot) &&
+    double tot[3];
+    if (reduce_last<3, 64 * WV>(part, partials, counter, nblocks, b, tot) &&
         threadIdx.x == 0) {
+        sc->mean_x = tot[2] * inv_area;
         sc->rr = tot[0];
         sc->rz = tot[0];
         sc->bb = tot[1];
@@ -477,7 +562,7 @@ __device__ __forceinline__ void cg_init_body(
 template <int N, class S, int WV, bool DIR = false, bool ISO = false>
 __device__ __forceinline__ void cg_dir_body(
     int b, Geom g, int tilesX, int nblocks, const OpConst<double>& k,
-    const S* __restrict__ r, S* p0, S* p1, double* __restrict__ x,
+    const S* r, S* p0, S* p1, double* __restrict__ x,
     CgScalars* sc, unsigned* counter, double* partials,
     YFaces<N, double, WV>& lds) {
     if (sc->done) return;
@@ -493,7 +578,10 @@ __device__ __forceinline__ void cg_dir_body(
     const int first = sc->first;
     const double alpha = sc->alpha;
     const double alpha_prev = sc->alpha_prev;
-    SrcDirection<N, S> src{r, pin, sc->beta, sc->cr, first == 1};
+    // the preconditioner leaves the first direction (z itself) where it belongs
+    const bool in_place = !kStoredLow<S> && first == 1 && sc->precond;
+    const S* rs = in_place ? pout : r;
+    SrcDirection<N, S> src{rs, pin, sc->beta, sc->cr, first == 1};
     double p[N * N], q[N * N], rv[N * N];
     if (c.active) {
         if (first != 1) {
@@ -513,7 +601,7 @@ __device__ __forceinline__ void cg_dir_body(
                 for (int e = 0; e < N * N; ++e) xv[e] = fmx(alpha, po[e], xv[e]);
                 st_l64<N>(x, c.self, xv);
             }
-            ld_l64<N>(r, c.self, p);
+            ld_l64<N>(rs, c.self, p);
 #pragma unroll
             for (int e = 0; e < N * N; ++e) {
                 rv[e] = p[e];
@@ -521,7 +609,7 @@ __device__ __forceinline__ void cg_dir_body(
                 p[e] = as_stored<S>(fmx(src.beta, po[e], ru));
             }
         } else {
-            ld_l64<N>(r, c.self, p);
+            ld_l64<N>(rs, c.self, p);
 #pragma unroll
             for (int e = 0; e < N * N; ++e) rv[e] = p[e];
         }
@@ -538,7 +626,7 @@ __device__ __forceinline__ void cg_dir_body(
 #pragma unroll
     for (int v = 0; v < NV; ++v) part[v] = 0.0;
     if (c.active) {
-        st_l64<N>(pout, c.self, p);
+        if (!in_place) st_l64<N>(pout, c.self, p);
 #pragma unroll
         for (int e = 0; e < N * N; ++e) q[e] = -q[e];
         part[0] = wdot_cell<N>(k, p, q);
@@ -553,6 +641,7 @@ __device__ __forceinline__ void cg_dir_body(
         if (tot[0] > 0.0 && tot[0] == tot[0]) {
             sc->alpha_prev = alpha;
             sc->alpha = (kStoredLow<S> ? tot[NV - 1] : sc->rz) / tot[0];
+            if (!kStoredLow<S> && sc->precond) sc->mean_x += sc->alpha * sc->mean_p;
         } else {  // breakdown (or non-finite data): stop; x lacks
                   // alpha_{k-1} p_{k-1} (still in pin) if its update waited
             sc->done = 1;
@@ -634,6 +723,7 @@ __device__ __forceinline__ void cg_res_body(
 // zero without rounding).  Partials <r64,r64>_W, <r32,r32>_W, <r32,p_last>_W.
 template <int N>
 struct SrcMixedX {
+    static constexpr bool kStaged = false;
     const double* x;
     const float* pl;
     double alpha;
@@ -721,9 +811,10 @@ __device__ __forceinline__ void mixed_replace_body(
 // Tiles of one cell-per-lane launch on a grid.
 struct CellLaunch {
     int tilesX, tilesY, nblocks;
-    __host__ __device__ explicit CellLaunch(const Geom& g) {
+    __host__ __device__ explicit CellLaunch(const Geom& g) : CellLaunch(g, g.cw) {}
+    __host__ __device__ CellLaunch(const Geom& g, int cw) {
         tilesX = (g.nx + 63) / 64;
-        tilesY = (g.ny + g.cw - 1) / g.cw;
+        tilesY = (g.ny + cw - 1) / cw;
         nblocks = tilesX * tilesY;
     }
 };

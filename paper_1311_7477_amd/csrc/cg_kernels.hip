@@ -13,7 +13,7 @@ template <int N, int WV, bool DIR, bool ISO>
 __global__ __launch_bounds__(64 * WV) void k_laplace(
     Geom g, int tilesX, int nblocks, OpConst<double> k,
     const double* __restrict__ u, double* __restrict__ out) {
-    __shared__ YFaces<N, double, WV> lds;
+    __shared__ LaplaceLds<N, WV> lds;
     laplace_body<N, WV, DIR, ISO>(blockIdx.x, g, tilesX, nblocks, k, u, out, lds);
 }
 
@@ -21,11 +21,11 @@ template <int N, int WV, bool DIR, bool ISO>
 __global__ __launch_bounds__(64 * WV) void k_cg_init(
     Geom g, int tilesX, int nblocks, OpConst<double> k,
     const double* __restrict__ omega, const double* __restrict__ pa,
-    const double* __restrict__ pb, double ca, double cb,
+    const double* __restrict__ pb, double ca, double cb, double inv_area,
     double* __restrict__ x, double* __restrict__ r, CgScalars* sc,
     unsigned* counter, double* partials) {
     __shared__ YFaces<N, double, WV> lds;
-    cg_init_body<N, WV, DIR, ISO>(blockIdx.x, g, tilesX, nblocks, k, omega, pa, pb, ca, cb, x,
+    cg_init_body<N, WV, DIR, ISO>(blockIdx.x, g, tilesX, nblocks, k, omega, pa, pb, ca, cb, inv_area, x,
                              r, sc, counter, partials, lds);
 }
 
@@ -35,7 +35,7 @@ __global__ __launch_bounds__(64 * WV) void k_cg_init(
 // lane the residual kernel then spills.
 template <int N, class S, int WV, bool DIR, bool ISO>
 __global__ __launch_bounds__(64 * WV, (N == 4 && !DIR) ? 4 : 1) void k_cg_dir(
-    Geom g, int tilesX, int nblocks, OpConst<double> k, const S* __restrict__ r,
+    Geom g, int tilesX, int nblocks, OpConst<double> k, const S* r,
     S* p0, S* p1, double* __restrict__ x, CgScalars* sc, unsigned* counter,
     double* partials) {
     __shared__ YFaces<N, double, WV> lds;
@@ -79,29 +79,29 @@ bool iso_dir(const Geom& g, const OpConst<double>& k) {
 
 hipError_t launch_laplace(const Geom& g, const OpConst<double>& k,
                           const double* u, double* out, hipStream_t s) {
-    CellLaunch L(g);
+    CellLaunch L(g, laplace_waves(g.n, g.cw));
     if (dirichlet(g)) {
         if (g.cw != kDirichletCellWaves) return hipErrorInvalidValue;
         if (iso_dir(g, k)) {
-            DG_DISPATCH_N(g.n, hipLaunchKernelGGL((k_laplace<NN, kDirichletCellWaves, true, true>),
-                                                  dim3(L.nblocks), dim3(64 * kDirichletCellWaves),
+            DG_DISPATCH_N(g.n, hipLaunchKernelGGL((k_laplace<NN, laplace_waves(NN, kDirichletCellWaves), true, true>),
+                                                  dim3(L.nblocks), dim3(64 * laplace_waves(NN, kDirichletCellWaves)),
                                                   0, s, g, L.tilesX, L.nblocks, k, u, out));
         } else {
-            DG_DISPATCH_N(g.n, hipLaunchKernelGGL((k_laplace<NN, kDirichletCellWaves, true, false>),
-                                                  dim3(L.nblocks), dim3(64 * kDirichletCellWaves),
+            DG_DISPATCH_N(g.n, hipLaunchKernelGGL((k_laplace<NN, laplace_waves(NN, kDirichletCellWaves), true, false>),
+                                                  dim3(L.nblocks), dim3(64 * laplace_waves(NN, kDirichletCellWaves)),
                                                   0, s, g, L.tilesX, L.nblocks, k, u, out));
         }
         return hipGetLastError();
     }
     if (iso(g, k)) {
-        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_laplace<NN, WW, false, true>),
+        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_laplace<NN, laplace_waves(NN, WW), false, true>),
                                                      dim3(L.nblocks),
-                                              dim3(64 * WW), 0, s, g, L.tilesX,
+                                              dim3(64 * laplace_waves(NN, WW)), 0, s, g, L.tilesX,
                                               L.nblocks, k, u, out));
     } else {
-        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_laplace<NN, WW, false, false>),
+        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_laplace<NN, laplace_waves(NN, WW), false, false>),
                                                      dim3(L.nblocks),
-                                              dim3(64 * WW), 0, s, g, L.tilesX,
+                                              dim3(64 * laplace_waves(NN, WW)), 0, s, g, L.tilesX,
                                               L.nblocks, k, u, out));
     }
     return hipGetLastError();
@@ -109,22 +109,23 @@ hipError_t launch_laplace(const Geom& g, const OpConst<double>& k,
 
 hipError_t launch_cg_init(const Geom& g, const OpConst<double>& k,
                           const double* omega, const double* pa,
-                          const double* pb, double ca, double cb, double* x,
+                          const double* pb, double ca, double cb, double area, double* x,
                           double* r, const DevScratch& d, hipStream_t s) {
     CellLaunch L(g);
+    const double inv_area = dirichlet(g) ? 0.0 : 1.0 / area;
     if (dirichlet(g)) {
         if (g.cw != kDirichletCellWaves) return hipErrorInvalidValue;
         if (iso_dir(g, k)) {
             DG_DISPATCH_N(g.n, hipLaunchKernelGGL((k_cg_init<NN, kDirichletCellWaves, true, true>),
                                                   dim3(L.nblocks), dim3(64 * kDirichletCellWaves),
                                                   0, s, g, L.tilesX, L.nblocks, k, omega, pa, pb,
-                                                  ca, cb, x, r, d.sc, d.counters + kCntInit * kCntStride,
+                                                  ca, cb, inv_area, x, r, d.sc, d.counters + kCntInit * kCntStride,
                                                   d.partials));
         } else {
             DG_DISPATCH_N(g.n, hipLaunchKernelGGL((k_cg_init<NN, kDirichletCellWaves, true, false>),
                                                   dim3(L.nblocks), dim3(64 * kDirichletCellWaves),
                                                   0, s, g, L.tilesX, L.nblocks, k, omega, pa, pb,
-                                                  ca, cb, x, r, d.sc, d.counters + kCntInit * kCntStride,
+                                                  ca, cb, inv_area, x, r, d.sc, d.counters + kCntInit * kCntStride,
                                                   d.partials));
         }
         return hipGetLastError();
@@ -133,13 +134,13 @@ hipError_t launch_cg_init(const Geom& g, const OpConst<double>& k,
         DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_cg_init<NN, WW, false, true>),
                                                      dim3(L.nblocks),
                                               dim3(64 * WW), 0, s, g, L.tilesX,
-                                              L.nblocks, k, omega, pa, pb, ca, cb, x, r,
+                                              L.nblocks, k, omega, pa, pb, ca, cb, inv_area, x, r,
                                               d.sc, d.counters + kCntInit * kCntStride, d.partials));
     } else {
         DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_cg_init<NN, WW, false, false>),
                                                      dim3(L.nblocks),
                                               dim3(64 * WW), 0, s, g, L.tilesX,
-                                              L.nblocks, k, omega, pa, pb, ca, cb, x, r,
+                                              L.nblocks, k, omega, pa, pb, ca, cb, inv_area, x, r,
                                               d.sc, d.counters + kCntInit * kCntStride, d.partials));
     }
     return hipGetLastError();

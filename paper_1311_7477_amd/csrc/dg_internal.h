@@ -106,13 +106,19 @@ struct CgScalars {
     double alpha_prev; // alpha of the iteration before the last (FP64
                        // directions: x takes two updates at a time)
     double tol2;      // rtol^2
-    double mean_omega, mean_x;
+    double mean_omega;
+    double mean_x;    // W-mean the finish removes from the solution (preconditioned:
+                      // of x with its pending updates, kept from the setup on)
     double ww;        // <omega, omega>_W
     double zero_tol2; // b counts as zero when <b,b>_W <= zero_tol2 * ww
     double ca, cb;    // guess = ca * psi_a + cb * psi_b (device copies)
     // mixed precision: <r,r>_W of the FP64 residual at the last replacement,
     // and the number of replacements
-    double rr_true, rr_true_prev;
+    union {
+        double rr_true;
+        double mean_p; // preconditioned: W-mean of the newest direction
+    };
+    double rr_true_prev;
     double rr_max;    // largest recursive <r,r>_W since the last replacement
     double cr;        // coefficient of r in the next direction (1 but right
                       // after a replacement)

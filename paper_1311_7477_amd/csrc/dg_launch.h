@@ -42,7 +42,7 @@ hipError_t launch_cg_mean(const Geom& g, const OpConst<double>& k,
 // x, r: lane-interleaved; omega, pa, pb: canonical
 hipError_t launch_cg_init(const Geom& g, const OpConst<double>& k,
                           const double* omega, const double* pa,
-                          const double* pb, double ca, double cb, double* x,
+                          const double* pb, double ca, double cb, double area, double* x,
                           double* r, const DevScratch& d, hipStream_t s);
 // CG iterations on vectors stored as S (double or float; the arithmetic is
 // FP64 either way); the direction buffers p0/p1 alternate by the device
@@ -83,6 +83,11 @@ hipError_t launch_cg_finish(const Geom& g, const OpConst<double>& k,
                             const double* x, const P* p0, const P* p1,
                             double* psi, double area, const DevScratch& d,
                             hipStream_t s);
+// The same at the end of a preconditioned solve, whose mean is known: psi =
+// x + pending alpha p - sc->mean_x in one pass
+hipError_t launch_pcg_finish(const Geom& g, const OpConst<double>& k, const double* x,
+                             const double* p0, const double* p1, double* psi,
+                             const DevScratch& d, hipStream_t s);
 // x (canonical) -= its W-mean
 hipError_t launch_mean_sub(const Geom& g, const OpConst<double>& k, double* x,
                            double area, const DevScratch& d, hipStream_t s);
@@ -117,8 +122,8 @@ hipError_t launch_from_image(const Geom& g, const OpConst<double>& k, const T* i
                              double* dst, hipStream_t s);
 template <class T>
 hipError_t launch_from_image_dot(const Geom& g, const OpConst<double>& k, const T* img,
-                                 bool dense, double* z, const double* r, const DevScratch& d,
-                                 hipStream_t s);
+                                 bool dense, double* z, double* z1, const double* r, double area,
+                                 const DevScratch& d, hipStream_t s);
 template <class T>
 hipError_t launch_dense_divide(int mx, int my, const T* lx, const T* ly, T* c, hipStream_t s);
 // The matrix-product path on node planes folded along x (E = u[c] +
@@ -131,8 +136,8 @@ hipError_t launch_to_planes_fold(const Geom& g, const double* src, bool from_l64
                                  hipStream_t s);
 template <class T>
 hipError_t launch_from_planes_fold(const Geom& g, const OpConst<double>& k, const T* img, int Kx,
-                                   double* dst, const double* r, const DevScratch* d,
-                                   hipStream_t s);
+                                   double* dst, double* z1, const double* r, double area,
+                                   const DevScratch* d, hipStream_t s);
 template <class T>
 hipError_t launch_fd_mix_x_fold(bool inverse, int n, int Nx, int Ny, int Ky, int K,
                                 const int* cols, const T* M, const T* in, T* out,

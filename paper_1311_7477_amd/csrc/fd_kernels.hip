@@ -86,7 +86,8 @@ __global__ __launch_bounds__(kPwThreads) void k_from_image(Geom g, OpConst<doubl
 // The last block of a <r, z>_W reduction: rz and, past the first iteration,
 // beta = <r,z>_new / <r,z>_old; a non-positive or non-finite <r,z> ends the
 // solve as a breakdown.
-__device__ __forceinline__ void set_rz(double rz, CgScalars* sc) {
+// mz: the W-mean of z; that of the direction follows the same recurrence.
+__device__ __forceinline__ void set_rz(double rz, double mz, CgScalars* sc) {
     sc->precond = 1;
     if (!(rz > 0.0) || !(rz < __builtin_inf())) {
         // <r, M r> must be positive and finite for a nonzero residual:
@@ -96,7 +97,12 @@ __device__ __forceinline__ void set_rz(double rz, CgScalars* sc) {
         sc->breakdown = 1;
         sc->pending = sc->first == 1 ? 0 : ((sc->iter & 1) ? 1 : 2);
     } else {
-        if (sc->first != 1) sc->beta = rz / sc->rz;
+        if (sc->first != 1) {
+            sc->beta = rz / sc->rz;
+            sc->mean_p = mz + sc->beta * sc->mean_p;
+        } else {
+            sc->mean_p = mz;
+        }
         sc->rz = rz;
     }
 }
@@ -140,12 +146,14 @@ __global__ __launch_bounds__(kPwThreads) void k_to_planes_fold(Geom g, const dou
 // or (Dot) lane-interleaved as z with <r, z>_W reduced as in k_from_image_dot.
 template <int N, bool Dot, class T>
 __global__ __launch_bounds__(kPwThreads) void k_from_planes_fold(
-    Geom g, OpConst<double> k, const T* __restrict__ img, int Kx, double* __restrict__ dst,
-    const double* __restrict__ r, CgScalars* sc, unsigned* counter, double* partials) {
+    Geom g, OpConst<double> k, const T* __restrict__ img, int Kx, double* dst, double* z1,
+    const double* __restrict__ r, double inv_area, CgScalars* sc, unsigned* counter,
+    double* partials) {
     if (Dot && sc->done) return;
+    if (Dot && sc->first == 1) dst = z1;
     const long pairs = (long)Kx * g.ny, cells = (long)g.nx * g.ny;
     const int G = (g.nx + 63) / 64;
-    double part[1] = {0.0};
+    double part[2] = {0.0, 0.0};
     for (long t = blockIdx.x * (long)kPwThreads + threadIdx.x; t < pairs;
          t += (long)gridDim.x * kPwThreads) {
         const int cy = (int)(t / Kx), c = (int)(t - (long)cy * Kx);
@@ -165,6 +173,7 @@ __global__ __launch_bounds__(kPwThreads) void k_from_planes_fold(
             st_l64<N>(dst, ca, a);
             ld_l64<N>(r, ca, rv);
             part[0] += wdot_cell<N>(k, rv, a);
+            part[1] += wsum_cell<N>(k, a);
         } else {
             st_canon<N>(dst, ca, a);
         }
@@ -175,32 +184,36 @@ __global__ __launch_bounds__(kPwThreads) void k_from_planes_fold(
                 st_l64<N>(dst, cb, b);
                 ld_l64<N>(r, cb, rv);
                 part[0] += wdot_cell<N>(k, rv, b);
+                part[1] += wsum_cell<N>(k, b);
             } else {
                 st_canon<N>(dst, cb, b);
             }
         }
     }
     if (Dot) {
-        double tot[1];
-        if (reduce_last<1, kPwThreads>(part, partials, counter, gridDim.x, blockIdx.x, tot) &&
+        double tot[2];
+        if (reduce_last<2, kPwThreads>(part, partials, counter, gridDim.x, blockIdx.x, tot) &&
             threadIdx.x == 0)
-            set_rz(tot[0], sc);
+            set_rz(tot[0], tot[1] * inv_area, sc);
     }
 }
 
-// z = image (to L64) and <r, z>_W; the last block sets rz and, past the
-// first iteration, beta = <r,z>_new / <r,z>_old (no-op once the solve is
+// z = image (to L64; at the first iteration z1, where the first direction
+// belongs) and <r, z>_W, <z, 1>_W; the last block sets rz and, past the first
+// iteration, beta = <r,z>_new / <r,z>_old (no-op once the solve is
 // done; a non-positive or non-finite <r,z> ends the solve as a breakdown).
 template <int N, bool Dense, class T>
 __global__ __launch_bounds__(kPwThreads) void k_from_image_dot(
-    Geom g, OpConst<double> k, const T* __restrict__ img, double* __restrict__ z,
-    const double* __restrict__ r, CgScalars* sc, unsigned* counter, double* partials) {
+    Geom g, OpConst<double> k, const T* __restrict__ img, double* z, double* z1,
+    const double* __restrict__ r, double inv_area, CgScalars* sc, unsigned* counter,
+    double* partials) {
     if (sc->done) return;
+    if (sc->first == 1) z = z1;
     const long cells = (long)g.nx * g.ny;
     const int G = (g.nx + 63) / 64;
     double sw[N * N];
     if (Dense) sqrt_w<N>(k, sw);
-    double part[1] = {0.0};
+    double part[2] = {0.0, 0.0};
     for (long cell = blockIdx.x * (long)kPwThreads + threadIdx.x; cell < cells;
          cell += (long)gridDim.x * kPwThreads) {
         const int cy = (int)(cell / g.nx), cx = (int)(cell - (long)cy * g.nx);
@@ -214,11 +227,12 @@ __global__ __launch_bounds__(kPwThreads) void k_from_image_dot(
         st_l64<N>(z, c, u);
         ld_l64<N>(r, c, rv);
         part[0] += wdot_cell<N>(k, rv, u);
+        part[1] += wsum_cell<N>(k, u);
     }
-    double tot[1];
-    if (reduce_last<1, kPwThreads>(part, partials, counter, gridDim.x, blockIdx.x, tot) &&
+    double tot[2];
+    if (reduce_last<2, kPwThreads>(part, partials, counter, gridDim.x, blockIdx.x, tot) &&
         threadIdx.x == 0)
-        set_rz(tot[0], sc);
+        set_rz(tot[0], tot[1] * inv_area, sc);
 }
 
 // out = M v for one 2n-vector (M row-major, S = 2n, row = output index);
@@ -881,17 +895,18 @@ hipError_t launch_from_image(const Geom& g, const OpConst<double>& k, const T* i
 
 template <class T>
 hipError_t launch_from_image_dot(const Geom& g, const OpConst<double>& k, const T* img,
-                                 bool dense, double* z, const double* r, const DevScratch& d,
-                                 hipStream_t s) {
+                                 bool dense, double* z, double* z1, const double* r, double area,
+                                 const DevScratch& d, hipStream_t s) {
+    const double inv_area = g.bcx || g.bcy ? 0.0 : 1.0 / area;
     const long cells = (long)g.nx * g.ny;
     const int nb = pw_blocks(cells, pointwise_block_cap());
     if (dense) {
         DG_DISPATCH_N(g.n, hipLaunchKernelGGL((k_from_image_dot<NN, true, T>), dim3(nb),
-                                              dim3(kPwThreads), 0, s, g, k, img, z, r, d.sc,
+                                              dim3(kPwThreads), 0, s, g, k, img, z, z1, r, inv_area, d.sc,
                                               d.counters + kCntDot * kCntStride, d.partials));
     } else {
         DG_DISPATCH_N(g.n, hipLaunchKernelGGL((k_from_image_dot<NN, false, T>), dim3(nb),
-                                              dim3(kPwThreads), 0, s, g, k, img, z, r, d.sc,
+                                              dim3(kPwThreads), 0, s, g, k, img, z, z1, r, inv_area, d.sc,
                                               d.counters + kCntDot * kCntStride, d.partials));
     }
     return hipGetLastError();
@@ -913,17 +928,17 @@ hipError_t launch_to_planes_fold(const Geom& g, const double* src, bool from_l64
 
 template <class T>
 hipError_t launch_from_planes_fold(const Geom& g, const OpConst<double>& k, const T* img, int Kx,
-                                   double* dst, const double* r, const DevScratch* d,
-                                   hipStream_t s) {
+                                   double* dst, double* z1, const double* r, double area,
+                                   const DevScratch* d, hipStream_t s) {
     const int nb = pw_blocks((long)Kx * g.ny, pointwise_block_cap());
     if (d) {
         DG_DISPATCH_N(g.n, hipLaunchKernelGGL((k_from_planes_fold<NN, true, T>), dim3(nb),
-                                              dim3(kPwThreads), 0, s, g, k, img, Kx, dst, r,
-                                              d->sc, d->counters + kCntDot * kCntStride, d->partials));
+                                              dim3(kPwThreads), 0, s, g, k, img, Kx, dst, z1, r,
+                                              1.0 / area, d->sc, d->counters + kCntDot * kCntStride, d->partials));
     } else {
         DG_DISPATCH_N(g.n, hipLaunchKernelGGL((k_from_planes_fold<NN, false, T>), dim3(nb),
                                               dim3(kPwThreads), 0, s, g, k, img, Kx, dst,
-                                              nullptr, nullptr, nullptr, nullptr));
+                                              nullptr, nullptr, 1.0, nullptr, nullptr, nullptr));
     }
     return hipGetLastError();
 }
@@ -1011,14 +1026,16 @@ hipError_t launch_fft_mix_y(int n, int Nx, int Ny, const int* cols, const T* Mf,
     template hipError_t launch_from_image<T>(const Geom&, const OpConst<double>&, const T*,    \
                                              bool, double*, hipStream_t);                      \
     template hipError_t launch_from_image_dot<T>(const Geom&, const OpConst<double>&,          \
-                                                 const T*, bool, double*, const double*,       \
-                                                 const DevScratch&, hipStream_t);              \
+                                                 const T*, bool, double*, double*,             \
+                                                 const double*, double, const DevScratch&,     \
+                                                 hipStream_t);              \
     template hipError_t launch_dense_divide<T>(int, int, const T*, const T*, T*, hipStream_t); \
     template hipError_t launch_to_planes_fold<T>(const Geom&, const double*, bool, int, T*,   \
                                                  hipStream_t);                                 \
     template hipError_t launch_from_planes_fold<T>(const Geom&, const OpConst<double>&,       \
-                                                   const T*, int, double*, const double*,     \
-                                                   const DevScratch*, hipStream_t);           \
+                                                   const T*, int, double*, double*,           \
+                                                   const double*, double, const DevScratch*,  \
+                                                   hipStream_t);           \
     template hipError_t launch_fd_mix_x_fold<T>(bool, int, int, int, int, int, const int*,    \
                                                 const T*, const T*, T*, hipStream_t);         \
     template hipError_t launch_fd_mix_y<T>(int, int, int, int, const int*, const T*, const T*, \

@@ -15,14 +15,15 @@ __global__ __launch_bounds__(kPwThreads) void k_cg_mean(
                     tol2, max_iter, dir, sc, counter, partials);
 }
 
-template <int N, class P>
+template <int N, class P, bool kMean>
 __global__ __launch_bounds__(kPwThreads) void k_cg_finish(
     Geom g, OpConst<double> k, const double* __restrict__ x,
     const P* __restrict__ p0, const P* __restrict__ p1,
     double* __restrict__ psi, double area, CgScalars* sc, unsigned* counter,
     double* partials) {
-    cg_finish_body<N, P>(blockIdx.x, gridDim.x, g, k, x, p0, p1, psi, area, sc,
-                      counter, partials);
+    __shared__ FinishLds<N> lds;
+    cg_finish_body<N, P, kMean>(blockIdx.x, gridDim.x, g, k, x, p0, p1, psi, area, sc,
+                                counter, partials, lds);
 }
 
 template <int N>
@@ -108,7 +109,7 @@ hipError_t launch_cg_finish(const Geom& g, const OpConst<double>& k,
                             hipStream_t s) {
     const long cells = (long)g.nx * g.ny;
     const int nb = pw_blocks(cells, pointwise_block_cap());
-    DG_DISPATCH_N(g.n, hipLaunchKernelGGL((k_cg_finish<NN, P>), dim3(nb),
+    DG_DISPATCH_N(g.n, hipLaunchKernelGGL((k_cg_finish<NN, P, false>), dim3(nb),
                                           dim3(kPwThreads), 0, s, g, k, x, p0, p1,
                                           psi, area, d.sc, d.counters + kCntFinish * kCntStride,
                                           d.partials));
@@ -126,6 +127,18 @@ template hipError_t launch_cg_finish<double>(const Geom&, const OpConst<double>&
 template hipError_t launch_cg_finish<float>(const Geom&, const OpConst<double>&,
                                             const double*, const float*, const float*,
                                             double*, double, const DevScratch&, hipStream_t);
+
+hipError_t launch_pcg_finish(const Geom& g, const OpConst<double>& k, const double* x,
+                             const double* p0, const double* p1, double* psi,
+                             const DevScratch& d, hipStream_t s) {
+    // (one group of 64 cells per wave: no reduction limits the blocks)
+    const long groups = (long)g.ny * ((g.nx + 63) / 64);
+    const int nb = (int)((groups + kPwThreads / 64 - 1) / (kPwThreads / 64));
+    DG_DISPATCH_N(g.n, hipLaunchKernelGGL((k_cg_finish<NN, double, true>), dim3(nb),
+                                          dim3(kPwThreads), 0, s, g, k, x, p0, p1, psi, 1.0,
+                                          d.sc, nullptr, nullptr));
+    return hipGetLastError();
+}
 
 hipError_t launch_mean_sub(const Geom& g, const OpConst<double>& k, double* x,
                            double area, const DevScratch& d, hipStream_t s) {

@@ -4,7 +4,7 @@
 // loops over node rows (canonical layout) or cells (layout conversion).
 #pragma once
 
-#include "dg_device.h"
+#include "cg_body.h"
 
 namespace dgk {
 
@@ -33,15 +33,29 @@ __device__ __forceinline__ void cg_mean_body(int b, int nb, long rows, const OpC
     (void)pa;
     (void)pb;
     double part[2] = {0.0, 0.0};
-    for (long row = b * (long)kPwThreads + threadIdx.x; row < rows;
-         row += (long)nb * kPwThreads) {
-        const int j = (int)(row % N);
-        double w[N], w2[N];
-        load_vec(omega, row * N, w);
+    // four rows in flight per thread
+    constexpr int U = 4;
+    const long step = (long)nb * kPwThreads;
+    for (long row0 = b * (long)kPwThreads + threadIdx.x; row0 < rows; row0 += U * step) {
+        double w[U][N];
 #pragma unroll
-        for (int i = 0; i < N; ++i) w2[i] = w[i] * w[i];
-        part[0] += wrow<N>(k, j, w);
-        part[1] += wrow<N>(k, j, w2);
+        for (int u = 0; u < U; ++u) {
+            if (row0 + u * step < rows) {
+                load_vec(omega, (row0 + u * step) * N, w[u]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < N; ++i) w[u][i] = 0.0;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = (int)((row0 + u * step) % N);
+            double w2[N];
+#pragma unroll
+            for (int i = 0; i < N; ++i) w2[i] = w[u][i] * w[u][i];
+            part[0] += wrow<N>(k, j, w[u]);
+            part[1] += wrow<N>(k, j, w2);
+        }
     }
     double tot[2];
     if (reduce_last<2, kPwThreads>(part, partials, counter, nb, b, tot) &&
@@ -70,46 +84,66 @@ __device__ __forceinline__ void cg_mean_body(int b, int nb, long rows, const OpC
 }
 
 // End of a solve: psi = x plus the pending updates or psi = 0 when b = 0,
-// converted from the lane-interleaved layout to canonical; partial W-mean.
-// pending = 1: x + alpha p_last (p_last = the buffer written by the last
-// direction update); 2: first alpha_prev times the other buffer (the
-// direction before), then alpha p_last.
-template <int N, class P>
+// converted from the lane-interleaved layout to canonical (a wave takes a group
+// of 64 cells and stages it); partial W-mean, or (kMean) minus the mean
+// sc->mean_x, known then: a preconditioned solve keeps the means of x and of its
+// directions from sums its kernels make anyway, which spares the pass that
+// subtracts the mean (n = 4, 512^2: 26.1 + 11.5 -> 17.3 us; n = 5, 1024^2: 176 +
+// 71 -> 116 us).  pending = 1: x + alpha p_last (p_last = the buffer
+// written by the last direction update); 2: first alpha_prev times the other
+// buffer (the direction before), then alpha p_last.
+template <int N>
+struct FinishLds {
+    alignas(16) double v[(kPwThreads / 64) * Stage<N>::SIZE];
+};
+
+template <int N, class P, bool kMean>
 __device__ __forceinline__ void cg_finish_body(int b, int nb, Geom g, const OpConst<double>& k, const double* __restrict__ x,
     const P* __restrict__ p0, const P* __restrict__ p1,
     double* __restrict__ psi, double area, CgScalars* sc, unsigned* counter,
-    double* partials) {
+    double* partials, FinishLds<N>& lds) {
     const int pending = sc->pending, zero = sc->zero;
     const double alpha = sc->alpha, alpha_prev = sc->alpha_prev;
+    const double mean = kMean ? sc->mean_x : 0.0;
     const P* pl = (sc->iter & 1) ? p1 : p0;
     const P* pb = (sc->iter & 1) ? p0 : p1;
-    const long cells = (long)g.nx * g.ny;
-    const int G = (g.nx + 63) / 64;
+    const int G = (g.nx + 63) / 64, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long groups = (long)g.ny * G;
+    double* buf = lds.v + wave * Stage<N>::SIZE;
     double part[1] = {0.0};
-    for (long cell = b * (long)kPwThreads + threadIdx.x; cell < cells;
-         cell += (long)nb * kPwThreads) {
-        const int cy = (int)(cell / g.nx), cx = (int)(cell - (long)cy * g.nx);
-        const long l64 = ((long)cy * G + (cx >> 6)) * (N * N * 64) + (cx & 63);
+    for (long q = (long)b * (kPwThreads / 64) + wave; q < groups;
+         q += (long)nb * (kPwThreads / 64)) {
+        const int cy = (int)(q / G), gx = (int)(q - (long)cy * G);
+        const int count = g.nx - gx * 64 < 64 ? g.nx - gx * 64 : 64;
+        CellRef c;
+        c.canon = 0;
+        c.l64 = q * (N * N * 64) + lane;
         double v[N * N];
+        zero_cell<N>(v);
+        if (!zero && lane < count) {
+            ld_l64<N>(x, c, v);
+            if (pending == 2) {
+                double w[N * N];
+                ld_l64<N>(pb, c, w);
 #pragma unroll
-        for (int e = 0; e < N * N; ++e) {
-            double a = 0.0;
-            if (!zero) {
-                a = x[l64_at<N>(l64, e)];
-                if (pending == 2) a = fmx(alpha_prev, (double)pb[l64_at<N>(l64, e)], a);
-                if (pending) a = fmx(alpha, (double)pl[l64_at<N>(l64, e)], a);
+                for (int e = 0; e < N * N; ++e) v[e] = fmx(alpha_prev, w[e], v[e]);
             }
-            v[e] = a;
-        }
-        store_vec(psi, cell * (N * N), v);
+            if (pending) {
+                double w[N * N];
+                ld_l64<N>(pl, c, w);
 #pragma unroll
-        for (int j = 0; j < N; ++j) {
-            double r[N];
+                for (int e = 0; e < N * N; ++e) v[e] = fmx(alpha, w[e], v[e]);
+            }
+            if (kMean) {
 #pragma unroll
-            for (int i = 0; i < N; ++i) r[i] = v[j * N + i];
-            part[0] += wrow<N>(k, j, r);
+                for (int e = 0; e < N * N; ++e) v[e] -= mean;
+            }
         }
+        stage_out<N>(psi + ((long)cy * g.nx + gx * 64) * (N * N), count, buf, lane, v);
+        if (!kMean && lane < count) part[0] += wsum_cell<N>(k, v);
     }
+    if (kMean) return;
     double tot[1];
     if (reduce_last<1, kPwThreads>(part, partials, counter, nb, b, tot) &&
         threadIdx.x == 0) {
@@ -150,20 +184,34 @@ __device__ __forceinline__ void invariants_body(int b, int nb, long rows, const 
     const double* __restrict__ psi, double* out3, unsigned* counter,
     double* partials) {
     double part[3] = {0.0, 0.0, 0.0};
-    for (long row = b * (long)kPwThreads + threadIdx.x; row < rows;
-         row += (long)nb * kPwThreads) {
-        const int j = (int)(row % N);
-        double w[N], p[N], pw[N], ww[N];
-        load_vec(omega, row * N, w);
-        load_vec(psi, row * N, p);
+    // two rows of each field in flight per thread
+    constexpr int U = 2;
+    const long step = (long)nb * kPwThreads;
+    for (long row0 = b * (long)kPwThreads + threadIdx.x; row0 < rows; row0 += U * step) {
+        double w[U][N], p[U][N];
 #pragma unroll
-        for (int i = 0; i < N; ++i) {
-            pw[i] = p[i] * w[i];
-            ww[i] = w[i] * w[i];
+        for (int u = 0; u < U; ++u) {
+            if (row0 + u * step < rows) {
+                load_vec(omega, (row0 + u * step) * N, w[u]);
+                load_vec(psi, (row0 + u * step) * N, p[u]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < N; ++i) w[u][i] = p[u][i] = 0.0;
+            }
         }
-        part[0] += wrow<N>(k, j, w);
-        part[1] += wrow<N>(k, j, pw);
-        part[2] += wrow<N>(k, j, ww);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = (int)((row0 + u * step) % N);
+            double pw[N], ww[N];
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                pw[i] = p[u][i] * w[u][i];
+                ww[i] = w[u][i] * w[u][i];
+            }
+            part[0] += wrow<N>(k, j, w[u]);
+            part[1] += wrow<N>(k, j, pw);
+            part[2] += wrow<N>(k, j, ww);
+        }
     }
     double tot[3];
     if (reduce_last<3, kPwThreads>(part, partials, counter, nb, b, tot) &&

@@ -30,7 +30,7 @@ int time_cg(dg_grid* g, const double* omega, dg_workspace* ws, int reps, hipEven
     hipError_t e = launch_cg_mean(geom, g->k64, omega, nullptr, nullptr, 0.0, 0.0, g->area,
                                   0.0, 1 << 30, ws->d, s);
     if (e == hipSuccess)
-        e = launch_cg_init(geom, g->k64, omega, nullptr, nullptr, 0.0, 0.0, ws->x, ws->r,
+        e = launch_cg_init(geom, g->k64, omega, nullptr, nullptr, 0.0, 0.0, g->area, ws->x, ws->r,
                            ws->d, s);
     const StepBuffers v{ws->x, ws->r, ws->s1, ws->p0, ws->p1, {ws->d.sc, ws->d.sc + 1},
                         ws->step_part, ws->step_max_blocks};
