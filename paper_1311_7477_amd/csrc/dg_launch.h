@@ -146,6 +146,24 @@ template <class T>
 hipError_t launch_fd_mix_y(int n, int Nx, int Ny, int K, const int* cols, const T* Mf,
                            const T* Mi, const T* lx, const T* ly, int zx, int zy, T* u,
                            hipStream_t s);
+// One or two matrix products of the transforms in one launch (fd_gemm.hip):
+// C_b = op(A_b) op(B_b) per half and batch, column-major, op = transpose where
+// asked (not both).  m, n: rows and columns of C, k: the summed index.
+template <class T>
+struct GemmHalf {
+    const T* A;
+    const T* B;
+    T* C;
+    int m, n, k;
+};
+template <class T>
+struct GemmPair {
+    GemmHalf<T> half[2];
+    long lda, ldb, ldc, sa, sb, sc;     // leading dimensions, batch strides
+};
+template <class T>
+hipError_t launch_gemm_pair(bool a_trans, bool b_trans, const GemmPair<T>& g, int halves, int batch,
+                            hipStream_t s);
 // The same mixing on the packed spectra of the FFTs along the cells (X, Y:
 // interleaved complex of type T, N/2 per real row; layouts in fd_kernels.hip).
 template <class T>

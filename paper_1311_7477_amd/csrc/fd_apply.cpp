@@ -72,6 +72,16 @@ int blas_fail(rocblas_status st, const char* what) {
 
 constexpr int kFdGemmMaxCells = 32;
 
+// The library's own product kernel (fd_gemm.hip) up to these operations per
+// transform, rocBLAS beyond.  Whole applications, own / rocBLAS, us: folded
+// pairs of halves, n = 3, 127 x 127 (1.8e7) 36 / 66, n = 4, 255 x 187 (1.7e8)
+// 81 / 107, 255 x 255 (2.7e8) 101 / 130, 401 x 401 (1.0e9) 264 / 233; single
+// dense products with walls, n = 3, 32 x 32 (1.8e6) 31 / 46, 128 x 128 (1.1e8)
+// 58 / 73, n = 4, 128 x 128 (2.7e8) 78 / 70: there the tiles of the library
+// fill the chip and reuse an operand more often.  Mixed-precision solves cross
+// at the same sizes.
+constexpr long long kOwnPairMaxFlops = 600000000, kOwnSingleMaxFlops = 200000000;
+
 int fft_fail(rocfft_status st, const char* what) {
     return fail(DG_E_HIP, "%s: rocFFT status %d", what, (int)st);
 }
@@ -146,61 +156,79 @@ rocblas_status gemm(rocblas_handle h, rocblas_operation ta, rocblas_operation tb
                                          &zero, C, ldc, sc, batch);
 }
 
+// The products of one transform: each half C = op(A) op(B), in one launch of
+// the library's own kernel up to the sizes above.
 template <class T>
-int apply_planes(const FdDevice* fd, hipStream_t s) {
+int products(const FdDevice* fd, rocblas_operation ta, rocblas_operation tb, const GemmPair<T>& g,
+             int halves, int batch, const char* what, hipStream_t s) {
+    long long flops = 0;
+    for (int i = 0; i < halves; ++i)
+        flops += 2LL * g.half[i].m * g.half[i].n * g.half[i].k * batch;
+    if (flops <= (halves == 2 ? kOwnPairMaxFlops : kOwnSingleMaxFlops)) {
+        const hipError_t e = launch_gemm_pair<T>(ta == rocblas_operation_transpose,
+                                                 tb == rocblas_operation_transpose, g, halves,
+                                                 batch, s);
+        return e == hipSuccess ? (int)DG_OK : hip_fail(e, what);
+    }
     rocblas_handle h = (rocblas_handle)fd->blas;
     rocblas_status st = rocblas_set_stream(h, s);
     if (st != rocblas_status_success) return blas_fail(st, "rocblas_set_stream");
+    for (int i = 0; i < halves; ++i) {
+        const GemmHalf<T>& p = g.half[i];
+        if (p.n == 0 || p.m == 0) continue;
+        st = gemm(h, ta, tb, p.m, p.n, p.k, p.A, (rocblas_int)g.lda, g.sa, p.B, (rocblas_int)g.ldb,
+                  g.sb, p.C, (rocblas_int)g.ldc, g.sc, batch);
+        if (st != rocblas_status_success) return blas_fail(st, what);
+    }
+    return DG_OK;
+}
+
+template <class T>
+int apply_planes(const FdDevice* fd, hipStream_t s) {
     const FdAxisDevice& X = fd->x;
     const FdAxisDevice& Y = fd->y;
     const FdFactorsDevice<T>& fx = X.get<T>();
     const FdFactorsDevice<T>& fy = Y.get<T>();
     T* u0 = reinterpret_cast<T*>(fd->img0);
     T* u1 = reinterpret_cast<T*>(fd->img1);
-    const rocblas_int n = fd->n, Nx = X.N, Ny = Y.N, M2 = n * n * Nx;
+    const int n = fd->n, Nx = X.N, Ny = Y.N, M2 = n * n * Nx;
     // even columns 0 .. Ke-1 and odd ones Ke .. N-1 of each (shifted) basis,
     // Ke = ceil(N/2); folded rows: E for c < Ke, O at Ke + c
-    const rocblas_int Kx = (Nx + 1) / 2, Sx = Nx - Kx, Ky = (Ny + 1) / 2, Sy = Ny - Ky;
-    const rocblas_int ldj = Ny * n;
-    const rocblas_stride plane_j = (rocblas_stride)Nx * Ny * n;   // one j of U / U1
+    const int Kx = (Nx + 1) / 2, Sx = Nx - Kx, Ky = (Ny + 1) / 2, Sy = Ny - Ky;
+    const int ldj = Ny * n;
+    const long plane_j = (long)Nx * Ny * n;   // one j of U / U1
     const rocblas_operation N_ = rocblas_operation_none, T_ = rocblas_operation_transpose;
     const T* phx_s = fx.phi + (size_t)Kx * Nx;   // rows 0 .. Sx-1 of the odd block
     const T* phy_s = fy.phi + (size_t)Ky * Ny;
     // x transform of the x-folded planes u0 (E rows 0 .. Kx-1, O rows Kx ..):
     // U1_j[:, even] = E_j^T Phi_x,even, U1_j[:, odd] = O_j^T Phi_x,odd
-    st = gemm(h, T_, N_, ldj, Kx, Kx, u0, Nx, plane_j, fx.phi, Nx, 0, u1, ldj, plane_j, n);
-    if (st == rocblas_status_success && Sx > 0)
-        st = gemm(h, T_, N_, ldj, Sx, Sx, u0 + Kx, Nx, plane_j, phx_s, Nx, 0,
-                  u1 + (size_t)Kx * ldj, ldj, plane_j, n);
-    if (st != rocblas_status_success) return blas_fail(st, "x transform");
+    int rc = products<T>(fd, T_, N_, {{{u0, fx.phi, u1, ldj, Kx, Kx},
+                                       {u0 + Kx, phx_s, u1 + (size_t)Kx * ldj, ldj, Sx, Sx}},
+                                      Nx, Nx, ldj, plane_j, 0, plane_j}, 2, n, "x transform", s);
+    if (rc != DG_OK) return rc;
     // x mixing (B^T W) and the fold along y: u1 -> u0
     hipError_t e = launch_fd_mix_x_fold<T>(false, n, Nx, Ny, Ky, X.K, X.cols, fx.mf, u1, u0, s);
     if (e != hipSuccess) return hip_fail(e, "x mixing launch");
     // y transform: U2 (M2 x Ny) from the y-folded rows of u0 (Ny x M2)
-    st = gemm(h, T_, N_, M2, Ky, Ky, u0, Ny, 0, fy.phi, Ny, 0, u1, M2, 0, 1);
-    if (st == rocblas_status_success && Sy > 0)
-        st = gemm(h, T_, N_, M2, Sy, Sy, u0 + Ky, Ny, 0, phy_s, Ny, 0, u1 + (size_t)Ky * M2, M2,
-                  0, 1);
-    if (st != rocblas_status_success) return blas_fail(st, "y transform");
+    rc = products<T>(fd, T_, N_, {{{u0, fy.phi, u1, M2, Ky, Ky},
+                                   {u0 + Ky, phy_s, u1 + (size_t)Ky * M2, M2, Sy, Sy}},
+                                  Ny, Ny, M2, 0, 0, 0}, 2, 1, "y transform", s);
+    if (rc != DG_OK) return rc;
     e = launch_fd_mix_y<T>(n, Nx, Ny, Y.K, Y.cols, fy.mf, fy.mi, fx.lam, fy.lam, X.zero, Y.zero,
                            u1, s);
     if (e != hipSuccess) return hip_fail(e, "y mixing launch");
     // inverse y transform into y-folded rows: u1 -> u0
-    st = gemm(h, N_, T_, Ky, M2, Ky, fy.phi, Ny, 0, u1, M2, 0, u0, Ny, 0, 1);
-    if (st == rocblas_status_success && Sy > 0)
-        st = gemm(h, N_, T_, Sy, M2, Sy, phy_s, Ny, 0, u1 + (size_t)Ky * M2, M2, 0, u0 + Ky, Ny,
-                  0, 1);
-    if (st != rocblas_status_success) return blas_fail(st, "inverse y transform");
+    rc = products<T>(fd, N_, T_, {{{fy.phi, u1, u0, Ky, M2, Ky},
+                                   {phy_s, u1 + (size_t)Ky * M2, u0 + Ky, Sy, M2, Sy}},
+                                  Ny, M2, Ny, 0, 0, 0}, 2, 1, "inverse y transform", s);
+    if (rc != DG_OK) return rc;
     // unfold along y and x unmixing (B): u0 -> u1
     e = launch_fd_mix_x_fold<T>(true, n, Nx, Ny, Ky, X.K, X.cols, fx.mi, u0, u1, s);
     if (e != hipSuccess) return hip_fail(e, "x unmixing launch");
     // inverse x transform into x-folded planes: u1 -> u0
-    st = gemm(h, N_, T_, Kx, ldj, Kx, fx.phi, Nx, 0, u1, ldj, plane_j, u0, Nx, plane_j, n);
-    if (st == rocblas_status_success && Sx > 0)
-        st = gemm(h, N_, T_, Sx, ldj, Sx, phx_s, Nx, 0, u1 + (size_t)Kx * ldj, ldj, plane_j,
-                  u0 + Kx, Nx, plane_j, n);
-    if (st != rocblas_status_success) return blas_fail(st, "inverse x transform");
-    return DG_OK;
+    return products<T>(fd, N_, T_, {{{fx.phi, u1, u0, Kx, ldj, Kx},
+                                     {phx_s, u1 + (size_t)Kx * ldj, u0 + Kx, Sx, ldj, Sx}},
+                                    Nx, ldj, Nx, 0, plane_j, plane_j}, 2, n, "inverse x transform", s);
 }
 
 template <class T>
@@ -401,28 +429,27 @@ int dense_axis(const dg_grid* g, int axis, rocblas_handle h, FdDenseAxis* out) {
 
 template <class T>
 int apply_dense(const FdDevice* fd, hipStream_t s) {
-    rocblas_handle h = (rocblas_handle)fd->blas;
-    rocblas_status st = rocblas_set_stream(h, s);
-    if (st != rocblas_status_success) return blas_fail(st, "rocblas_set_stream");
     const FdDenseAxis& X = fd->dx;
     const FdDenseAxis& Y = fd->dy;
-    const rocblas_int mx = X.m, my = Y.m;
+    const int mx = X.m, my = Y.m;
     T* a = reinterpret_cast<T*>(fd->img0);
     T* b = reinterpret_cast<T*>(fd->img1);
     const T* qx = X.q<T>();
     const T* qy = Y.q<T>();
     const rocblas_operation N_ = rocblas_operation_none, T_ = rocblas_operation_transpose;
-    st = gemm(h, T_, N_, mx, my, mx, qx, mx, 0, a, mx, 0, b, mx, 0, 1);          // B = Qx^T A
-    if (st == rocblas_status_success)
-        st = gemm(h, N_, N_, mx, my, my, b, mx, 0, qy, my, 0, a, mx, 0, 1);      // A = B Qy
-    if (st != rocblas_status_success) return blas_fail(st, "dense forward transform");
+    auto one = [&](rocblas_operation ta, rocblas_operation tb, const T* A, int lda, const T* B,
+                   int ldb, T* C, int k, const char* what) {
+        return products<T>(fd, ta, tb, {{{A, B, C, mx, my, k}, {}}, lda, ldb, mx, 0, 0, 0}, 1, 1,
+                           what, s);
+    };
+    int rc = one(T_, N_, qx, mx, a, mx, b, mx, "dense forward transform");            // B = Qx^T A
+    if (rc == DG_OK) rc = one(N_, N_, b, mx, qy, my, a, my, "dense forward transform");   // A = B Qy
+    if (rc != DG_OK) return rc;
     hipError_t e = launch_dense_divide<T>(mx, my, X.lam<T>(), Y.lam<T>(), a, s);
     if (e != hipSuccess) return hip_fail(e, "dense spectral division launch");
-    st = gemm(h, N_, N_, mx, my, mx, qx, mx, 0, a, mx, 0, b, mx, 0, 1);          // B = Qx A
-    if (st == rocblas_status_success)
-        st = gemm(h, N_, T_, mx, my, my, b, mx, 0, qy, my, 0, a, mx, 0, 1);      // A = B Qy^T
-    if (st != rocblas_status_success) return blas_fail(st, "dense inverse transform");
-    return DG_OK;
+    rc = one(N_, N_, qx, mx, a, mx, b, mx, "dense inverse transform");                // B = Qx A
+    if (rc == DG_OK) rc = one(N_, T_, b, mx, qy, my, a, my, "dense inverse transform");   // A = B Qy^T
+    return rc;
 }
 
 // One batched 1D complex FFT of length H = L/2 along an axis of L cells:
