@@ -346,7 +346,7 @@ int cg_mixed(const dg_grid* g, const double* omega, double* x, const double* pa,
 
 // z = M r on node planes in the precision T, then z and <r, z>_W in FP64
 // (device scalars in d.sc).  The first z is the first direction and goes where
-// the direction kernel would store it (iteration 0 writes p1).
+// the direction kernels look for it (iteration 0's is p1).
 template <class T>
 int precond_step(const dg_grid* g, dg_workspace* ws, const DevScratch& d, hipStream_t s) {
     T* planes = reinterpret_cast<T*>(ws->fd->img0);
@@ -368,20 +368,15 @@ int precond_step(const dg_grid* g, dg_workspace* ws, const DevScratch& d, hipStr
     return DG_OK;
 }
 
-int pcg_iteration(const dg_grid* g, bool fp32, const DevScratch& d, dg_workspace* ws,
-                  hipStream_t s);
-
-// Queue the setup of a preconditioned solve and `iters` iterations (z = M r
-// on node planes -- cell Fourier transforms + per-wave-number mixing --
-// then the direction / residual kernels with p built from z) on the device
-// scalars d.sc, reading nothing back.  Once the device flag says the solve
-// is done the CG kernels exit at once; the preconditioner's library
-// transforms of a later iteration still run.  fp32: M is applied in FP32
-// (the mixed-precision form: the solve's bulk work in FP32, every residual,
-// solution and step length in FP64, so the FP64 iteration refines the FP32
-// solves).
+// Queue the setup of a preconditioned solve, its first iteration (z = M r on
+// node planes -- cell Fourier transforms + per-wave-number mixing -- then r -= A
+// z and psi = x + z minus its mean) on the device scalars d.sc, reading nothing
+// back.  When the setup finds the solve done the CG kernels only write psi; the
+// preconditioner's transforms still run.  fp32: M is applied in FP32 (the
+// mixed-precision form: the solve's bulk work in FP32, every residual and
+// solution in FP64, so the FP64 iteration refines the FP32 solves).
 int pcg_queue(const dg_grid* g, const double* omega, const double* pa, double ca,
-              const double* pb, double cb, const dg_cg_opts& o, bool fp32, int iters,
+              const double* pb, double cb, const dg_cg_opts& o, bool fp32, double* psi,
               const DevScratch& d, dg_workspace* ws, hipStream_t s) {
     const double tol2 = o.rtol * o.rtol;
     hipError_t e = launch_cg_mean(g->geom, g->k64, omega, pa, pb, ca, cb, g->area, tol2,
@@ -389,13 +384,14 @@ int pcg_queue(const dg_grid* g, const double* omega, const double* pa, double ca
     if (e != hipSuccess) return hip_fail(e, "cg mean launch");
     e = launch_cg_init(g->geom, g->k64, omega, pa, pb, ca, cb, g->area, ws->x, ws->r, d, s);
     if (e != hipSuccess) return hip_fail(e, "cg init launch");
-    for (int it = 0; it < iters; ++it) {
-        int rc = pcg_iteration(g, fp32, d, ws, s);
-        if (rc != DG_OK) return rc;
-    }
+    int rc = fp32 ? precond_step<float>(g, ws, d, s) : precond_step<double>(g, ws, d, s);
+    if (rc != DG_OK) return rc;
+    e = launch_pcg_first(g->geom, g->k64, ws->x, ws->p1, ws->r, psi, d, s);
+    if (e != hipSuccess) return hip_fail(e, "pcg first iteration launch");
     return DG_OK;
 }
 
+// A later iteration: direction p = z + beta p and residual kernels.
 int pcg_iteration(const dg_grid* g, bool fp32, const DevScratch& d, dg_workspace* ws,
                   hipStream_t s) {
     int rc = fp32 ? precond_step<float>(g, ws, d, s) : precond_step<double>(g, ws, d, s);
@@ -432,11 +428,13 @@ int pcg_result(const CgScalars& h, dg_cg_stats* st) {
 int cg_pcg(const dg_grid* g, const double* omega, double* x, const double* pa,
            double ca, const double* pb, double cb, const dg_cg_opts& o, bool fp32,
            dg_cg_stats* st, dg_workspace* ws, hipStream_t s) {
-    int rc = pcg_queue(g, omega, pa, ca, pb, cb, o, fp32, 1, ws->d, ws, s);
+    int rc = pcg_queue(g, omega, pa, ca, pb, cb, o, fp32, x, ws->d, ws, s);
     if (rc != DG_OK) return rc;
     rc = read_scalars(ws, ws->d.sc, &ws->host[2], s);
     if (rc != DG_OK) return rc;
     CgScalars h = ws->host[2];
+    // the first iteration has written psi
+    if (h.done && !h.breakdown) return pcg_result(h, st);
     while (!h.done) {
         rc = pcg_iteration(g, fp32, ws->d, ws, s);
         if (rc != DG_OK) return rc;
@@ -849,7 +847,7 @@ constexpr int kRedo = 1;   // a queued step must be taken again synchronously
 
 // One SSP-RK3 step with the three preconditioned stage solves queued ahead
 // of any convergence check: each stage runs the setup, one PCG iteration
-// (the exact preconditioner's usual count), the finish and the fused RHS
+// (the exact preconditioner's usual count; it writes psi) and the fused RHS
 // kernel, on its own device scalars; the host reads the three stages'
 // scalars once, at the end.  omega is saved first and the psi history the
 // step starts from stays in the state's reserved buffers, so when a stage
@@ -881,13 +879,11 @@ int rk_step_queued(const dg_grid* g, double* omega, dg_state* st, const dg_step_
         state_guess(st, ts[k], &pa, &ca, &pb, &cb, &x, &fr);
         DevScratch d = ws->d;
         d.sc = ws->sc3 + k;
-        int rc = pcg_queue(g, win[k], pa, ca, pb, cb, opts->cg, false, 1, d, ws, s);
+        int rc = pcg_queue(g, win[k], pa, ca, pb, cb, opts->cg, false, x, d, ws, s);
         if (rc != DG_OK) return rc;
-        hipError_t e = launch_pcg_finish(g->geom, g->k64, ws->x, ws->p0, ws->p1, x, d, s);
-        if (e != hipSuccess) return hip_fail(e, "cg finish launch");
         state_push(st, fr, ts[k]);
         RhsParams p{fc[0], fc[1], fc[2], fc[3], opts->D, dt, ra[k], rb[k], 0};
-        e = launch_rhs(g->geom, g->k64, x, win[k], k ? omega : nullptr, wout[k], p, true, s);
+        hipError_t e = launch_rhs(g->geom, g->k64, x, win[k], k ? omega : nullptr, wout[k], p, true, s);
         if (e != hipSuccess) return hip_fail(e, "rhs launch");
         if (timing) HIP_TRY(hipEventRecord(ws->tev[k + 1], s));
     }

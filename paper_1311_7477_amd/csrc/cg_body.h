@@ -578,10 +578,7 @@ __device__ __forceinline__ void cg_dir_body(
     const int first = sc->first;
     const double alpha = sc->alpha;
     const double alpha_prev = sc->alpha_prev;
-    // the preconditioner leaves the first direction (z itself) where it belongs
-    const bool in_place = !kStoredLow<S> && first == 1 && sc->precond;
-    const S* rs = in_place ? pout : r;
-    SrcDirection<N, S> src{rs, pin, sc->beta, sc->cr, first == 1};
+    SrcDirection<N, S> src{r, pin, sc->beta, sc->cr, first == 1};
     double p[N * N], q[N * N], rv[N * N];
     if (c.active) {
         if (first != 1) {
@@ -601,7 +598,7 @@ __device__ __forceinline__ void cg_dir_body(
                 for (int e = 0; e < N * N; ++e) xv[e] = fmx(alpha, po[e], xv[e]);
                 st_l64<N>(x, c.self, xv);
             }
-            ld_l64<N>(rs, c.self, p);
+            ld_l64<N>(r, c.self, p);
 #pragma unroll
             for (int e = 0; e < N * N; ++e) {
                 rv[e] = p[e];
@@ -609,7 +606,7 @@ __device__ __forceinline__ void cg_dir_body(
                 p[e] = as_stored<S>(fmx(src.beta, po[e], ru));
             }
         } else {
-            ld_l64<N>(rs, c.self, p);
+            ld_l64<N>(r, c.self, p);
 #pragma unroll
             for (int e = 0; e < N * N; ++e) rv[e] = p[e];
         }
@@ -626,7 +623,7 @@ __device__ __forceinline__ void cg_dir_body(
 #pragma unroll
     for (int v = 0; v < NV; ++v) part[v] = 0.0;
     if (c.active) {
-        if (!in_place) st_l64<N>(pout, c.self, p);
+        st_l64<N>(pout, c.self, p);
 #pragma unroll
         for (int e = 0; e < N * N; ++e) q[e] = -q[e];
         part[0] = wdot_cell<N>(k, p, q);

@@ -88,6 +88,15 @@ hipError_t launch_cg_finish(const Geom& g, const OpConst<double>& k,
 hipError_t launch_pcg_finish(const Geom& g, const OpConst<double>& k, const double* x,
                              const double* p0, const double* p1, double* psi,
                              const DevScratch& d, hipStream_t s);
+// The first iteration and the finish of a preconditioned solve in one kernel
+// (pcg_kernels.hip): r -= A z, psi = x + z minus the mean, the convergence test.
+hipError_t launch_pcg_first(const Geom& g, const OpConst<double>& k, const double* x,
+                            const double* z, double* r, double* psi, const DevScratch& d,
+                            hipStream_t s);
+// Boundary kinds and square cells: the variants a cell-per-lane launch takes
+bool dirichlet(const Geom& g);
+bool iso(const Geom& g, const OpConst<double>& k);
+bool iso_dir(const Geom& g, const OpConst<double>& k);
 // x (canonical) -= its W-mean
 hipError_t launch_mean_sub(const Geom& g, const OpConst<double>& k, double* x,
                            double area, const DevScratch& d, hipStream_t s);

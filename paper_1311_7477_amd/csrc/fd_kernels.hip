@@ -83,26 +83,26 @@ __global__ __launch_bounds__(kPwThreads) void k_from_image(Geom g, OpConst<doubl
     }
 }
 
-// The last block of a <r, z>_W reduction: rz and, past the first iteration,
-// beta = <r,z>_new / <r,z>_old; a non-positive or non-finite <r,z> ends the
-// solve as a breakdown.
+// The last block of a <r, z>_W reduction: rz and beta = <r,z>_new / <r,z>_old
+// (0 after the first iteration, whose step length is 1 and needs no <r,z>: rz is
+// 0 then); a non-positive or non-finite <r,z> ends the solve as a breakdown.
 // mz: the W-mean of z; that of the direction follows the same recurrence.
 __device__ __forceinline__ void set_rz(double rz, double mz, CgScalars* sc) {
-    sc->precond = 1;
+    if (sc->first == 1) {
+        sc->precond = 1;
+        sc->mean_p = mz;
+        return;
+    }
     if (!(rz > 0.0) || !(rz < __builtin_inf())) {
         // <r, M r> must be positive and finite for a nonzero residual:
         // stop; x still lacks the last alpha p after any iteration, and the
         // one before it after an odd one (iter = the next iteration's k)
         sc->done = 1;
         sc->breakdown = 1;
-        sc->pending = sc->first == 1 ? 0 : ((sc->iter & 1) ? 1 : 2);
+        sc->pending = (sc->iter & 1) ? 1 : 2;
     } else {
-        if (sc->first != 1) {
-            sc->beta = rz / sc->rz;
-            sc->mean_p = mz + sc->beta * sc->mean_p;
-        } else {
-            sc->mean_p = mz;
-        }
+        sc->beta = sc->rz > 0.0 ? rz / sc->rz : 0.0;
+        sc->mean_p = mz + sc->beta * sc->mean_p;
         sc->rz = rz;
     }
 }
@@ -150,7 +150,8 @@ __global__ __launch_bounds__(kPwThreads) void k_from_planes_fold(
     const double* __restrict__ r, double inv_area, CgScalars* sc, unsigned* counter,
     double* partials) {
     if (Dot && sc->done) return;
-    if (Dot && sc->first == 1) dst = z1;
+    const bool first = Dot && sc->first == 1;     // no <r, z> then
+    if (first) dst = z1;
     const long pairs = (long)Kx * g.ny, cells = (long)g.nx * g.ny;
     const int G = (g.nx + 63) / 64;
     double part[2] = {0.0, 0.0};
@@ -169,10 +170,12 @@ __global__ __launch_bounds__(kPwThreads) void k_from_planes_fold(
         }
         const CellRef ca = cell_ref<N>(g, G, c, cy);
         if (Dot) {
-            double rv[N * N];
             st_l64<N>(dst, ca, a);
-            ld_l64<N>(r, ca, rv);
-            part[0] += wdot_cell<N>(k, rv, a);
+            if (!first) {
+                double rv[N * N];
+                ld_l64<N>(r, ca, rv);
+                part[0] += wdot_cell<N>(k, rv, a);
+            }
             part[1] += wsum_cell<N>(k, a);
         } else {
             st_canon<N>(dst, ca, a);
@@ -180,10 +183,12 @@ __global__ __launch_bounds__(kPwThreads) void k_from_planes_fold(
         if (pr) {
             const CellRef cb = cell_ref<N>(g, G, g.nx - 1 - c, cy);
             if (Dot) {
-                double rv[N * N];
                 st_l64<N>(dst, cb, b);
-                ld_l64<N>(r, cb, rv);
-                part[0] += wdot_cell<N>(k, rv, b);
+                if (!first) {
+                    double rv[N * N];
+                    ld_l64<N>(r, cb, rv);
+                    part[0] += wdot_cell<N>(k, rv, b);
+                }
                 part[1] += wsum_cell<N>(k, b);
             } else {
                 st_canon<N>(dst, cb, b);
@@ -199,16 +204,16 @@ __global__ __launch_bounds__(kPwThreads) void k_from_planes_fold(
 }
 
 // z = image (to L64; at the first iteration z1, where the first direction
-// belongs) and <r, z>_W, <z, 1>_W; the last block sets rz and, past the first
-// iteration, beta = <r,z>_new / <r,z>_old (no-op once the solve is
-// done; a non-positive or non-finite <r,z> ends the solve as a breakdown).
+// belongs), <z, 1>_W and, past the first iteration, <r, z>_W; the last block
+// sets rz and beta (no-op once the solve is done).
 template <int N, bool Dense, class T>
 __global__ __launch_bounds__(kPwThreads) void k_from_image_dot(
     Geom g, OpConst<double> k, const T* __restrict__ img, double* z, double* z1,
     const double* __restrict__ r, double inv_area, CgScalars* sc, unsigned* counter,
     double* partials) {
     if (sc->done) return;
-    if (sc->first == 1) z = z1;
+    const bool first = sc->first == 1;
+    if (first) z = z1;
     const long cells = (long)g.nx * g.ny;
     const int G = (g.nx + 63) / 64;
     double sw[N * N];
@@ -218,15 +223,18 @@ __global__ __launch_bounds__(kPwThreads) void k_from_image_dot(
          cell += (long)gridDim.x * kPwThreads) {
         const int cy = (int)(cell / g.nx), cx = (int)(cell - (long)cy * g.nx);
         const CellRef c = cell_ref<N>(g, G, cx, cy);
-        double u[N * N], rv[N * N];
+        double u[N * N];
 #pragma unroll
         for (int q = 0; q < N * N; ++q) {
             u[q] = (double)img[fd_at<N, Dense>(g, cell, cx, cy, q)];
             if (Dense) u[q] /= sw[q];
         }
         st_l64<N>(z, c, u);
-        ld_l64<N>(r, c, rv);
-        part[0] += wdot_cell<N>(k, rv, u);
+        if (!first) {
+            double rv[N * N];
+            ld_l64<N>(r, c, rv);
+            part[0] += wdot_cell<N>(k, rv, u);
+        }
         part[1] += wsum_cell<N>(k, u);
     }
     double tot[2];
