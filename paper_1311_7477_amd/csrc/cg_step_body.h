@@ -60,18 +60,6 @@ struct StepLaunch {
     }
 };
 
-// The value of lane + 1 / lane - 1 (the wave's ends wrap round).
-__device__ __forceinline__ double lane_next(double v) {
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x134, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x134, 0xf, 0xf, false);
-    return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double lane_prev(double v) {
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x13c, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x13c, 0xf, 0xf, false);
-    return __hiloint2double(hi, lo);
-}
-
 template <int CTRL>
 __device__ __forceinline__ double add_dpp(double v) {
     const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, false);

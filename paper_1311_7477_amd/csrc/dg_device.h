@@ -29,6 +29,18 @@ __device__ __forceinline__ int xcd_tile(int b, int nblocks) {
     return xcd < r ? xcd * (q + 1) + idx : r * (q + 1) + (xcd - r) * q + idx;
 }
 
+// The value of lane + 1 / lane - 1 (the wave's ends wrap round).
+__device__ __forceinline__ double lane_next(double v) {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x134, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x134, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double lane_prev(double v) {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x13c, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x13c, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+
 template <int M, class T>
 __device__ __forceinline__ void load_vec(const T* __restrict__ f, long off,
                                          T (&u)[M]) {

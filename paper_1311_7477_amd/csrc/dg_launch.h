@@ -155,6 +155,12 @@ template <class T>
 hipError_t launch_fd_mix_y(int n, int Nx, int Ny, int K, const int* cols, const T* Mf,
                            const T* Mi, const T* lx, const T* ly, int zx, int zy, T* u,
                            hipStream_t s);
+// The bracket / right-hand side by strips (rhs_strip.hip), and whether a grid
+// takes it
+bool rhs_strips(const Geom& g);
+hipError_t launch_rhs_strip(const Geom& g, const OpConst<double>& k, const double* f,
+                            const double* gg, const double* wn, double* out, const RhsArgs& ra,
+                            bool visc, hipStream_t s);
 // One or two matrix products of the transforms in one launch (fd_gemm.hip):
 // C_b = op(A_b) op(B_b) per half and batch, column-major, op = transpose where
 // asked (not both).  m, n: rows and columns of C, k: the summed index.

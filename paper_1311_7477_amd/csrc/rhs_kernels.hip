@@ -1,5 +1,5 @@
-// Single-instance launch of the fused bracket / right-hand-side kernel (row
-// per lane; the device code is in rhs_body.h).
+// Single-instance launch of the fused bracket / right-hand-side kernel: row per
+// lane (rhs_body.h), or strips on the larger periodic grids (rhs_strip.hip).
 #include "dg_launch.h"
 #include "rhs_body.h"
 
@@ -21,6 +21,8 @@ hipError_t launch_rhs(const Geom& g, const OpConst<double>& k, const double* f,
                       const double* gg, const double* wn, double* out,
                       const RhsParams& p, bool visc, hipStream_t s) {
     RhsArgs ra{p.c0, p.c1, p.c2, p.scale, p.D, p.dt, p.a, p.b, p.only_r};
+    if (rhs_strips(g))
+        return launch_rhs_strip(g, k, f, gg, wn, out, ra, visc, s);
     DG_DISPATCH_NR(g.n, g.rw, {
         RowLaunch L(g);
         // a Dirichlet axis takes the variants with the boundary faces
