@@ -346,16 +346,20 @@ int cg_mixed(const dg_grid* g, const double* omega, double* x, const double* pa,
 
 // z = M r on node planes in the precision T, then z and <r, z>_W in FP64
 // (device scalars in d.sc).  The first z is the first direction and goes where
-// the direction kernels look for it (iteration 0's is p1).
+// the direction kernels look for it (iteration 0's is p1).  placed: the setup has
+// put r into the work field, unless that holds folded planes.
 template <class T>
-int precond_step(const dg_grid* g, dg_workspace* ws, const DevScratch& d, hipStream_t s) {
+int precond_step(const dg_grid* g, dg_workspace* ws, const DevScratch& d, bool placed,
+                 hipStream_t s) {
     T* planes = reinterpret_cast<T*>(ws->fd->img0);
     const int layout = fd_layout(ws->fd);
     const bool dense = layout == kFdDense;
     const int Kx = (g->nx + 1) / 2;
-    hipError_t e = layout == kFdFolded
-                       ? launch_to_planes_fold<T>(g->geom, ws->r, true, Kx, planes, s)
-                       : launch_to_image<T>(g->geom, g->k64, ws->r, true, dense, planes, s);
+    hipError_t e = hipSuccess;
+    if (layout == kFdFolded)
+        e = launch_to_planes_fold<T>(g->geom, ws->r, true, Kx, planes, s);
+    else if (!placed)
+        e = launch_to_image<T>(g->geom, g->k64, ws->r, true, dense, planes, s);
     if (e != hipSuccess) return hip_fail(e, "image conversion launch");
     int rc = fd_apply_image(ws->fd, sizeof(T) == sizeof(float), s);
     if (rc != DG_OK) return rc;
@@ -382,9 +386,17 @@ int pcg_queue(const dg_grid* g, const double* omega, const double* pa, double ca
     hipError_t e = launch_cg_mean(g->geom, g->k64, omega, pa, pb, ca, cb, g->area, tol2,
                                   o.max_iter, d, s);
     if (e != hipSuccess) return hip_fail(e, "cg mean launch");
-    e = launch_cg_init(g->geom, g->k64, omega, pa, pb, ca, cb, g->area, ws->x, ws->r, d, s);
+    InitImage img;
+    const int layout = fd_layout(ws->fd);
+    img.dense = layout == kFdDense;
+    if (layout != kFdFolded) {
+        if (fp32) img.f = reinterpret_cast<float*>(ws->fd->img0);
+        else img.d = ws->fd->img0;
+    }
+    e = launch_cg_init(g->geom, g->k64, omega, pa, pb, ca, cb, g->area, ws->x, ws->r, d, s, img);
     if (e != hipSuccess) return hip_fail(e, "cg init launch");
-    int rc = fp32 ? precond_step<float>(g, ws, d, s) : precond_step<double>(g, ws, d, s);
+    int rc = fp32 ? precond_step<float>(g, ws, d, true, s)
+                  : precond_step<double>(g, ws, d, true, s);
     if (rc != DG_OK) return rc;
     e = launch_pcg_first(g->geom, g->k64, ws->x, ws->p1, ws->r, psi, d, s);
     if (e != hipSuccess) return hip_fail(e, "pcg first iteration launch");
@@ -394,7 +406,8 @@ int pcg_queue(const dg_grid* g, const double* omega, const double* pa, double ca
 // A later iteration: direction p = z + beta p and residual kernels.
 int pcg_iteration(const dg_grid* g, bool fp32, const DevScratch& d, dg_workspace* ws,
                   hipStream_t s) {
-    int rc = fp32 ? precond_step<float>(g, ws, d, s) : precond_step<double>(g, ws, d, s);
+    int rc = fp32 ? precond_step<float>(g, ws, d, false, s)
+                  : precond_step<double>(g, ws, d, false, s);
     if (rc != DG_OK) return rc;
     hipError_t e = launch_cg_dir<double>(g->geom, g->k64, ws->x, ws->z, ws->p0, ws->p1, d.sc,
                                          d, s);

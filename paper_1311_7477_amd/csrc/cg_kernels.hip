@@ -23,10 +23,10 @@ __global__ __launch_bounds__(64 * WV) void k_cg_init(
     const double* __restrict__ omega, const double* __restrict__ pa,
     const double* __restrict__ pb, double ca, double cb, double inv_area,
     double* __restrict__ x, double* __restrict__ r, CgScalars* sc,
-    unsigned* counter, double* partials) {
+    unsigned* counter, double* partials, InitImage img) {
     __shared__ YFaces<N, double, WV> lds;
     cg_init_body<N, WV, DIR, ISO>(blockIdx.x, g, tilesX, nblocks, k, omega, pa, pb, ca, cb, inv_area, x,
-                             r, sc, counter, partials, lds);
+                             r, sc, counter, partials, lds, img);
 }
 
 // At n = 4 the periodic direction and residual kernels are held to 128
@@ -110,7 +110,7 @@ hipError_t launch_laplace(const Geom& g, const OpConst<double>& k,
 hipError_t launch_cg_init(const Geom& g, const OpConst<double>& k,
                           const double* omega, const double* pa,
                           const double* pb, double ca, double cb, double area, double* x,
-                          double* r, const DevScratch& d, hipStream_t s) {
+                          double* r, const DevScratch& d, hipStream_t s, const InitImage& img) {
     CellLaunch L(g);
     const double inv_area = dirichlet(g) ? 0.0 : 1.0 / area;
     if (dirichlet(g)) {
@@ -120,13 +120,13 @@ hipError_t launch_cg_init(const Geom& g, const OpConst<double>& k,
                                                   dim3(L.nblocks), dim3(64 * kDirichletCellWaves),
                                                   0, s, g, L.tilesX, L.nblocks, k, omega, pa, pb,
                                                   ca, cb, inv_area, x, r, d.sc, d.counters + kCntInit * kCntStride,
-                                                  d.partials));
+                                                  d.partials, img));
         } else {
             DG_DISPATCH_N(g.n, hipLaunchKernelGGL((k_cg_init<NN, kDirichletCellWaves, true, false>),
                                                   dim3(L.nblocks), dim3(64 * kDirichletCellWaves),
                                                   0, s, g, L.tilesX, L.nblocks, k, omega, pa, pb,
                                                   ca, cb, inv_area, x, r, d.sc, d.counters + kCntInit * kCntStride,
-                                                  d.partials));
+                                                  d.partials, img));
         }
         return hipGetLastError();
     }
@@ -135,13 +135,13 @@ hipError_t launch_cg_init(const Geom& g, const OpConst<double>& k,
                                                      dim3(L.nblocks),
                                               dim3(64 * WW), 0, s, g, L.tilesX,
                                               L.nblocks, k, omega, pa, pb, ca, cb, inv_area, x, r,
-                                              d.sc, d.counters + kCntInit * kCntStride, d.partials));
+                                              d.sc, d.counters + kCntInit * kCntStride, d.partials, img));
     } else {
         DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_cg_init<NN, WW, false, false>),
                                                      dim3(L.nblocks),
                                               dim3(64 * WW), 0, s, g, L.tilesX,
                                               L.nblocks, k, omega, pa, pb, ca, cb, inv_area, x, r,
-                                              d.sc, d.counters + kCntInit * kCntStride, d.partials));
+                                              d.sc, d.counters + kCntInit * kCntStride, d.partials, img));
     }
     return hipGetLastError();
 }

@@ -96,6 +96,14 @@ struct RhsArgs {
     int only_r;
 };
 
+// The preconditioner's work field, in FP64 or FP32, for the CG setup to fill
+// (neither: it does not); dense: as the image the eigenbasis path takes.
+struct InitImage {
+    double* d = nullptr;
+    float* f = nullptr;
+    int dense = 0;
+};
+
 // Device-side scalars of one CG solve (lives in the workspace).
 struct CgScalars {
     double rr;        // <r, r>_W of the current residual

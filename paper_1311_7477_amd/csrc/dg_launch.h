@@ -43,7 +43,8 @@ hipError_t launch_cg_mean(const Geom& g, const OpConst<double>& k,
 hipError_t launch_cg_init(const Geom& g, const OpConst<double>& k,
                           const double* omega, const double* pa,
                           const double* pb, double ca, double cb, double area, double* x,
-                          double* r, const DevScratch& d, hipStream_t s);
+                          double* r, const DevScratch& d, hipStream_t s,
+                          const InitImage& img = InitImage());
 // CG iterations on vectors stored as S (double or float; the arithmetic is
 // FP64 either way); the direction buffers p0/p1 alternate by the device
 // iteration count (sc->iter), so any number of queued no-op iterations

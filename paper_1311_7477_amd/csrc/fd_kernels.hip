@@ -17,29 +17,6 @@ namespace dgk {
 
 namespace {
 
-// Where node q = i + n j of cell (cx, cy) sits in the work field: node
-// planes [cell + nx ny q], or (Dense, the eigenbasis path of grids with a
-// Dirichlet axis) the image [(cx + nx i) + n nx (cy + ny j)], a column-major
-// (n nx) x (n ny) matrix whose rows run along x.  Consecutive cells along x
-// stay consecutive either way.
-template <int N, bool Dense>
-__device__ __forceinline__ long fd_at(const Geom& g, long cell, int cx, int cy, int q) {
-    if (!Dense) return cell + (long)g.nx * g.ny * q;
-    const int i = q % N, j = q / N;
-    return cx + (long)g.nx * i + (long)N * g.nx * (cy + (long)g.ny * j);
-}
-
-// sqrt(W) at the nodes of one cell (the dense path works with the
-// orthogonal Q = W^{1/2} V, so fields enter scaled by sqrt(W) and leave
-// scaled by its inverse)
-template <int N>
-__device__ __forceinline__ void sqrt_w(const OpConst<double>& k, double (&sw)[N * N]) {
-#pragma unroll
-    for (int j = 0; j < N; ++j)
-#pragma unroll
-        for (int i = 0; i < N; ++i) sw[j * N + i] = sqrt(k.w[i] * k.w[j] * k.wq);
-}
-
 template <int N, bool FromL64, bool Dense, class T>
 __global__ __launch_bounds__(kPwThreads) void k_to_image(Geom g, OpConst<double> k,
                                                          const double* __restrict__ src,
