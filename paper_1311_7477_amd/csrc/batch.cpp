@@ -126,7 +126,9 @@ int rebuild_lists(dg_batch* b, hipStream_t s) {
         const BatchInst& r = b->h_inst[i];
         const int gi = group_of(r.g);
         mask.set(gi);
-        const int counts[kListCount] = {r.cell_nblocks, r.step_nblocks, r.row_nblocks,
+        // (members whose right-hand side goes by strips launch it alone)
+        const int rows = rhs_strips(r.g) ? 0 : r.row_nblocks;
+        const int counts[kListCount] = {r.cell_nblocks, r.step_nblocks, rows,
                                         r.nb_rows, r.nb_cells, r.nb_elems};
         for (int k = 0; k < kListCount; ++k)
             for (int q = 0; q < counts[k]; ++q) h[gi][k].push_back(BatchItem{i, q});
@@ -557,6 +559,14 @@ int dg_batch_rk_step(dg_batch* b, const dg_cg_opts* opts, int* iters_out,
         if (rc != DG_OK) return rc;
         rc = run(b, enqueue_finish, b->g_finish, s);
         if (rc != DG_OK) return rc;
+        // the members large enough to take the strip kernel fill the chip alone
+        for (int i = 0; i < b->capacity; ++i) {
+            const BatchInst& r = b->h_inst[i];
+            if (!b->slots[i].used || !rhs_strips(r.g)) continue;
+            const hipError_t e = launch_rhs_strip(r.g, r.k, r.psi, r.w_in, r.w_n, r.w_out, r.ra,
+                                                  true, s);
+            if (e != hipSuccess) return hip_fail(e, "batch right-hand side launch");
+        }
         CgScalars* fin = b->h_sc;
         HIP_TRY(hipMemcpyAsync(fin, b->d_sc, b->capacity * sizeof(CgScalars),
                                hipMemcpyDeviceToHost, s));

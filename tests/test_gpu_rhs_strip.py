@@ -78,3 +78,23 @@ def test_rk_step():
     assert dg.rk_step(grid, w, dg.State(grid), ws, dt, D, opts).converged
     e = w.cpu().numpy() - ref
     assert math.sqrt(O.inner(g, e, e)) <= 1e-12 * math.sqrt(O.inner(g, ref, ref))
+
+
+# a batch with members on both kernels: bitwise as stepped alone
+@pytest.mark.parametrize("graphs", [True, False])
+def test_batch_members(graphs):
+    from paper_1311_7477_amd import dg
+    print(f"strip batch graphs={graphs}", flush=True)
+    opts, dt, D = dg.cg_opts(rtol=1e-3), 1e-5, 1e-4
+    batch, inst = dg.Batch(3, use_graphs=graphs), []
+    for n, nx, ny in ((3, 621, 745), (3, 40, 30), (4, 620, 615)):
+        grid = dg.Grid(n, nx, ny)
+        w0 = dev(I.random_modes(n, nx, ny, seed=nx))
+        w = w0.clone()
+        inst.append((batch.attach(grid, w, dt, D), grid, w0, w))
+    assert batch.rk_step(opts)[1]
+    for slot, grid, w0, w in inst:
+        st = dg.State(grid)
+        dg.rk_step(grid, w0, st, dg.Workspace(grid), dt, D, opts)
+        assert torch.equal(w, w0)
+        assert torch.equal(batch.psi(slot), st.psi())
