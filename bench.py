@@ -1044,9 +1044,9 @@ def main():
             "algorithmic_bytes_per_launch": alg_bytes,
             "copy_GBps": copy_gbs,
             "frac_of_copy": achieved / copy_gbs,
-            "cache_note": ("the CG vectors (3 fields, %.0f MB) fit the 256 MB Infinity "
+            "cache_note": ("the CG vectors (5 fields, %.0f MB) fit the 256 MB Infinity "
                            "Cache at this size, so this is effective bandwidth; the "
-                           "HBM-bound figure is profiled at n=5, 1024^2" % (3 * F / 1e6)),
+                           "HBM-bound figure is profiled at n=5, 1024^2" % (5 * F / 1e6)),
         },
     }
     if not args.no_precond:

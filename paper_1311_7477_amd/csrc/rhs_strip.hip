@@ -12,10 +12,11 @@
 // the cells in its halos: bracket n = 5, 2048^2 876 -> 660 us (3.8 TB/s), n = 4,
 // 2048^2 456 -> 387, 1024^2 115 -> 102, n = 3, 2048^2 262 -> 195, n = 2, 2048^2 122
 // -> 88, n = 1, 2048^2 29 -> 21; with the viscous term and the stage combination
-// n = 5, 1024^2 317 -> 262.  What bounds it from n = 4 on is one wave per SIMD: a
-// cell's two fields, its sums, the traces and the row ahead take 300 - 500
-// registers, so a row costs its 2500 instructions (n = 5) plus every latency the
-// one wave cannot hide.  (Held to two waves, n = 4 spills: 489 us at 2048^2.)
+// n = 5, 1024^2 317 -> 253.  What bounds it from n = 4 on are its FP64 instructions
+// (1400 a row of cells at n = 4, 2400 at n = 5), on one wave per SIMD: a cell's
+// two fields, its sums, the traces and the row ahead take 300 - 500 registers.  A
+// second wave hides little more: n = 4 without the row ahead fits two, 2048^2 387
+// -> 369 us, and then spills with the viscous term.
 #include "dg_launch.h"
 #include "dg_stage.h"
 
