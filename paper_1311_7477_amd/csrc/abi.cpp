@@ -222,9 +222,10 @@ int cg_steps(const dg_grid* g, const double* omega, const dg_cg_opts& o, dg_work
     // the second residual takes the RK field that does not hold the input
     StepBuffers v{ws->x, ws->r, omega == ws->s1 ? ws->s2 : ws->s1, ws->p0, ws->p1,
                   {ws->d.sc, ws->d.sc + 1}, ws->step_part, ws->step_max_blocks};
-    const int chunk = o.check_every > 0 ? (o.check_every + (o.check_every & 1)) : 32;
     const int most = o.max_iter < (1 << 30) ? o.max_iter : (1 << 30);
     const int total = (most + 3) & ~1;
+    const int every = o.check_every > 0 ? o.check_every : 32;
+    const int chunk = every < total ? (every + 1) & ~1 : total;
     int round = -1;
     return cg_loop(total, chunk, ws->d.sc, ws, s, fin, [&](int launch, int i, int slot) {
         // the sampled launch alternates between the first and the second of a

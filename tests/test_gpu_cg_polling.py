@@ -1,0 +1,26 @@
+"""How often a solve is polled, and how many iterations it is allowed, change
+neither its result nor its end, up to the largest values of their type."""
+import pytest
+
+from paper_1311_7477_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+INT_MAX = 2 ** 31 - 1
+
+
+@pytest.mark.parametrize("every", [1, 2, 7, 2000, 2001, INT_MAX - 1, INT_MAX])
+def test_check_every(every):
+    from paper_1311_7477_amd import dg
+    print(f"cg check_every={every}", flush=True)
+    grid = dg.Grid(3, 20, 18)
+    w = torch.from_numpy(I.white_noise(3, 20, 18, seed=1)).cuda()
+    out = []
+    for e in (0, every):
+        psi = torch.zeros_like(w)
+        res = dg.cg_solve_poisson(grid, w, psi, dg.Workspace(grid),
+                                  dg.cg_opts(rtol=1e-12, max_iter=2000, check_every=e))
+        assert res.converged
+        out.append((res.iters, psi))
+    assert out[0][0] == out[1][0] and torch.equal(out[0][1], out[1][1])
