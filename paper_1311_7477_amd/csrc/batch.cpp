@@ -278,7 +278,7 @@ int run_chunks(dg_batch* b, const dg_cg_opts& o, hipStream_t s) {
             HIP_TRY(hipStreamWaitEvent(b->lane[l], b->fork, 0));
             live[l] = of_lane[l];
         }
-        int issued = 0;
+        long issued = 0;      // (max_iter may be the largest int)
         for (int round = 0;; ++round) {
             const int slot = round & 1;
             bool any = false;
@@ -301,7 +301,7 @@ int run_chunks(dg_batch* b, const dg_cg_opts& o, hipStream_t s) {
             }
             if (!any) break;
             issued += b->chunk;
-            if (issued >= o.max_iter + b->chunk) break;
+            if (issued >= (long)o.max_iter + b->chunk) break;
             if (round == 0) continue;
             for (int l = 0; l < lanes; ++l) {
                 if (live[l].none()) continue;

@@ -24,3 +24,18 @@ def test_check_every(every):
         assert res.converged
         out.append((res.iters, psi))
     assert out[0][0] == out[1][0] and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("graphs", [True, False])
+def test_batch_iterations_allowed(graphs):
+    from paper_1311_7477_amd import dg
+    print(f"batch max_iter graphs={graphs}", flush=True)
+    w0 = torch.from_numpy(I.white_noise(3, 20, 18, seed=1)).cuda()
+    out = []
+    for most in (100000, INT_MAX):
+        batch, w = dg.Batch(1, use_graphs=graphs), w0.clone()
+        slot = batch.attach(dg.Grid(3, 20, 18), w, 1e-4, 1e-3)
+        iters, ok = batch.rk_step(dg.cg_opts(rtol=1e-12, max_iter=most))
+        assert ok
+        out.append((iters[slot], w))
+    assert out[0][0] == out[1][0] and torch.equal(out[0][1], out[1][1])
