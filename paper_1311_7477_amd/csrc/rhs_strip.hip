@@ -24,18 +24,24 @@ namespace dgk {
 
 namespace {
 
-// The centred derivative is odd under reflection: C0[i][m] = -C0[n-1-i][n-1-m],
-// cL[i] = -cR[n-1-i], sL[i] = sR[n-1-i].  On sums and differences of mirrored
-// values u[p] +- u[n-1-p] it takes half the products, its traces and face terms
-// likewise: with p, i < h = n / 2 and c the middle index of an odd n,
-//   res[i], res[n-1-i] = y_i +- x_i,  res[c] = mid . o + cc (fR - fL)
-//   x_i = sum_p xe[i][p] e_p + xc[i] u[c] + t[i] (fR + fL)
+// The centred derivative is odd under reflection (C0[i][m] = -C0[n-1-i][n-1-m],
+// cL[i] = -cR[n-1-i], sL[i] = sR[n-1-i]) and annihilates constants (the sR sum to
+// one).  On the sums e_p = u[p] - 2 u[h] + u[n-1-p] and differences o_p = u[p] -
+// u[n-1-p] of mirrored values it takes half the products, its traces and face
+// terms likewise: with p, i < h = n / 2,
+//   res[i], res[n-1-i] = y_i +- x_i,  res[h] = mid . o + cc (fR - fL) for odd n
+//   x_i = sum_p xe[i][p] e_p + t[i] (fR - 2 u[h] + fL)
 //   y_i = sum_p yo[i][p] o_p + d[i] (fR - fL)
-//   sR . u, sL . u = (se . e + sc u[c]) +- so . o
+//   sR . u, sL . u = (u[h] + se . e) +- so . o
+// Sums of the mirrored values themselves would be rounded at twice the size of a
+// field that the derivative then cancels: the bracket of smooth fields was 1.2 (n =
+// 2) to 1.5 times (n = 5) as far from the exact one as with plain products.  The
+// sums less 2 u[h] are small and rounded at the field's size once, before the last
+// addition: 0.85 to 0.95 times as far.
 template <int N>
 struct Mirror {
     static constexpr int H = N / 2, M = H > 0 ? H : 1;
-    double xe[M][M], xc[M], t[M], yo[M][M], d[M], mid[M], cc, se[M], so[M], sc;
+    double xe[M][M], t[M], yo[M][M], d[M], mid[M], cc, se[M], so[M];
     explicit Mirror(const OpConst<double>& k) {
         for (int i = 0; i < H; ++i) {
             const int r = N - 1 - i;
@@ -43,7 +49,6 @@ struct Mirror {
                 xe[i][p] = 0.5 * (k.C0[i * N + p] + k.C0[i * N + N - 1 - p]);
                 yo[i][p] = 0.5 * (k.C0[i * N + p] - k.C0[i * N + N - 1 - p]);
             }
-            xc[i] = N % 2 ? k.C0[i * N + H] : 0.0;
             t[i] = 0.5 * (k.cR[i] - k.cR[r]);
             d[i] = 0.5 * (k.cR[i] + k.cR[r]);
             mid[i] = N % 2 ? k.C0[H * N + i] : 0.0;
@@ -51,7 +56,6 @@ struct Mirror {
             so[i] = 0.5 * (k.sR[i] - k.sR[r]);
         }
         cc = N % 2 ? k.cR[H] : 0.0;
-        sc = N % 2 ? k.sR[H] : 0.0;
     }
 };
 
@@ -73,24 +77,23 @@ template <int N>
 __device__ __forceinline__ void row_deriv(const Mirror<N>& q, const double (&u)[N],
                                           double (&res)[N]) {
     constexpr int H = N / 2;
-    double e[H + 1], o[H + 1], P = 0, Q = 0;
+    const double c = u[H];
+    double e[H + 1], o[H + 1], P = c, Q = 0;
 #pragma unroll
     for (int p = 0; p < H; ++p) {
-        e[p] = u[p] + u[N - 1 - p];
         o[p] = u[p] - u[N - 1 - p];
+        e[p] = 2 * p + 2 == N ? o[p] : fmx(-2.0, c, u[p]) + u[N - 1 - p];
     }
-    if (N % 2) P = q.sc * u[H];
 #pragma unroll
     for (int p = 0; p < H; ++p) {
-        P = (p == 0 && N % 2 == 0) ? q.se[p] * e[p] : fmx(q.se[p], e[p], P);
+        P = fmx(q.se[p], e[p], P);
         Q = p == 0 ? q.so[p] * o[p] : fmx(q.so[p], o[p], Q);
     }
     const double fR = lane_next(P + Q), fL = lane_prev(P - Q);
-    const double T = fR + fL, D = fR - fL;
+    const double T = fmx(-2.0, c, fR) + fL, D = fR - fL;
 #pragma unroll
     for (int i = 0; i < H; ++i) {
         double x = q.t[i] * T, y = q.d[i] * D;
-        if (N % 2) x = fmx(q.xc[i], u[H], x);
 #pragma unroll
         for (int p = 0; p < H; ++p) {
             x = fmx(q.xe[i][p], e[p], x);
@@ -307,7 +310,7 @@ __global__ __launch_bounds__(64, N >= 4 ? 1 : 2) void k_rhs_strip(
     take();
     for (int y = y0; y < y1; ++y) {
         wave_lds_fence();
-    strip_put<N>(vF, lF, lane);
+        strip_put<N>(vF, lF, lane);
         strip_put<N>(vG, lG, lane);
         if (y + 1 < y1) {
             strip_load<N>(f + row_of(y + 2), gg + row_of(y + 2), st, lane, vF, vG);
