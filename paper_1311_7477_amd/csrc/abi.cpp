@@ -221,7 +221,7 @@ int cg_steps(const dg_grid* g, const double* omega, const dg_cg_opts& o, dg_work
              hipStream_t s, CgScalars* fin) {
     // the second residual takes the RK field that does not hold the input
     StepBuffers v{ws->x, ws->r, omega == ws->s1 ? ws->s2 : ws->s1, ws->p0, ws->p1,
-                  {ws->d.sc, ws->d.sc + 1}, ws->step_part, ws->step_max_blocks};
+                  {ws->d.sc, ws->d.sc + 1}, g->scale, ws->step_part, ws->step_max_blocks};
     const int most = o.max_iter < (1 << 30) ? o.max_iter : (1 << 30);
     const int total = (most + 3) & ~1;
     const int every = o.check_every > 0 ? o.check_every : 32;
@@ -572,6 +572,7 @@ int dg_grid_create(int n, int nx, int ny, double x0, double x1, double y0,
     g->geom = Geom{n, nx, ny, kCellWavesDefault, kRowWavesDefault,
                    bc_x == DG_BC_DIRICHLET ? 1 : 0, bc_y == DG_BC_DIRICHLET ? 1 : 0};
     fill_const(*g, g->k64);
+    g->scale = lap_scale(n, g->k64);
     g->elems = (size_t)nx * ny * n * n;
     *out = g;
     return DG_OK;

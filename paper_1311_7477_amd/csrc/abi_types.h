@@ -17,6 +17,7 @@ struct dg_grid {
     double x0, x1, y0, y1, hx, hy, area;
     HostTables t;
     OpConst<double> k64;
+    dgk::LapScale scale;
     Geom geom;
     size_t elems;
 };

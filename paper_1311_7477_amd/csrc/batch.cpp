@@ -420,6 +420,7 @@ int dg_batch_attach(dg_batch* b, const dg_grid* g, double* omega, double dt,
     fill_batch_geometry(r);
     r.area = g->area;
     r.k = g->k64;
+    r.scale = g->scale;
     r.active = 1;
     r.x = sl.ws->x;
     r.r = sl.ws->r;

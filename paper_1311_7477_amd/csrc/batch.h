@@ -27,6 +27,7 @@ struct BatchInst {
     double area, tol2;
     int max_iter, active;
     OpConst<double> k;
+    LapScale scale;
     // stage part
     const double* w_in;    // omega of this stage (solve input, bracket input)
     const double* w_n;     // omega at the start of the step (null at stage 1)

@@ -52,7 +52,7 @@ __global__ __launch_bounds__(64 * WV, (N <= 4 ? 4 : 1)) void kb_cg_step(const Ba
     __shared__ StepLds<N, WV> lds;
     DG_FOR_ITEMS(list) {
         const size_t stride = step_part_stride(B.step_max_blocks);
-        cg_step_body<N, WV, false>(item_.b, B.g, B.step_tilesX, B.step_nblocks, B.k, PAR,
+        cg_step_body<N, WV, false>(item_.b, B.g, B.step_tilesX, B.step_nblocks, B.k, B.scale, PAR,
                                    PAR ? B.r1 : B.r, PAR ? B.r : B.r1, PAR ? B.p1 : B.p0,
                                    PAR ? B.p0 : B.p1, B.x, PAR ? B.sc1 : B.sc,
                                    PAR ? B.sc : B.sc1, B.step_part + PAR * stride,

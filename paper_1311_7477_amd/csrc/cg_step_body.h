@@ -13,6 +13,8 @@
 // and sums <p_k, A p_k>, <A p_k, A p_k>, <r_k, A p_k>, <r_k, r_k>, from which
 // the next launch takes its scalars.  A p_{k-1} is formed again here instead
 // of being stored: reading and writing it would be two more fields.
+// A is formed in units of its size (LapScale, a power of two: every rounding as
+// without it), so that <q, q> overflows no earlier than <r, r> and <p, A p>.
 // Per launch: read r, p; write r, p (4 fields); every other one also p_{k-2}
 // and x (7 fields) -- 5.5 on average against 7.5 of the two-launch form.
 // Microseconds per iteration, two launches -> this kernel: n = 3, 128^2
@@ -104,11 +106,11 @@ struct StepLds {
     double red[WV * 4 * kStepSums];
 };
 
-// Lap_h u at node (j, i) from the cell's values and its face scalars.
+// Lap_h u (times sl.unit) at node (j, i) from the cell's values and its face scalars.
 template <int N, bool ISO>
-__device__ __forceinline__ double lap_node(const OpConst<double>& k, const double (&u)[N * N],
-                                           int j, int i, double fR, double fL, double fU,
-                                           double fD) {
+__device__ __forceinline__ double lap_node(const OpConst<double>& k, const LapScale& sl,
+                                           const double (&u)[N * N], int j, int i, double fR,
+                                           double fL, double fU, double fD) {
     const double* L0y = ISO ? k.L0x : k.L0y;
     const double* eRy = ISO ? k.eRx : k.eRy;
     double lx = fmx(k.eRx[i], fR, k.eL[i] * fL);
@@ -118,7 +120,7 @@ __device__ __forceinline__ double lap_node(const OpConst<double>& k, const doubl
         lx = fmx(k.L0x[i * N + m], u[j * N + m], lx);
         ly = fmx(L0y[j * N + m], u[m * N + i], ly);
     }
-    return fmx(lx, k.ihx2, ly * k.ihy2);
+    return fmx(lx, sl.x, ly * sl.y);
 }
 
 // x += ap pp + a p on one cell (n >= 4: in parts of at most eight nodes, so
@@ -158,7 +160,7 @@ __device__ __forceinline__ void add_to_x(double* __restrict__ x, const double* p
 // part_in, this launch's go to sc_out and part_out.
 template <int N, int WV, bool ISO>
 __device__ __forceinline__ void cg_step_body(
-    int b, Geom g, int tilesX, int nblocks, const OpConst<double>& k, int par,
+    int b, Geom g, int tilesX, int nblocks, const OpConst<double>& k, const LapScale& sl, int par,
     const double* __restrict__ rin, double* __restrict__ rout, const double* __restrict__ pin,
     double* __restrict__ pout, double* __restrict__ x, const CgScalars* __restrict__ sc_in,
     CgScalars* __restrict__ sc_out, const double* __restrict__ part_in, double* part_out,
@@ -243,7 +245,7 @@ __device__ __forceinline__ void cg_step_body(
             const double next = fmx(alpha, fmx(alpha, qq, -2.0 * rq), rr);
             beta = next > 0.0 ? next / rr : 0.0;
             s.alpha_prev = s.alpha;
-            s.alpha = alpha;
+            s.alpha = alpha * sl.unit;
             s.beta = beta;
             s.iter += 1;
         }
@@ -251,6 +253,10 @@ __device__ __forceinline__ void cg_step_body(
     s.first = 0;
     if (b == 0 && threadIdx.x == 0) *sc_out = s;
     if (s.done) return;
+    // (the same in every lane: held once)
+    alpha = read_lane(alpha, 0);
+    beta = read_lane(beta, 0);
+    const double ax = read_lane(s.alpha, 0), ax_prev = read_lane(s.alpha_prev, 0);
 
     double fR[N], fL[N];
     // this cell's face scalars to the neighbouring waves and lanes
@@ -278,7 +284,7 @@ __device__ __forceinline__ void cg_step_body(
             const double fU = face[FR + i * 64], fD = face[-FR + (N + i) * 64];
 #pragma unroll
             for (int j = 0; j < N; ++j)
-                r[j * N + i] = fmx(alpha, lap_node<N, ISO>(k, p, j, i, fR[j], fL[j], fU, fD),
+                r[j * N + i] = fmx(alpha, lap_node<N, ISO>(k, sl, p, j, i, fR[j], fL[j], fU, fD),
                                    r[j * N + i]);
         }
 #pragma unroll
@@ -297,7 +303,7 @@ __device__ __forceinline__ void cg_step_body(
             double a[kStepSums] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
             for (int j = 0; j < N; ++j) {
-                const double q = lap_node<N, ISO>(k, p, j, i, fR[j], fL[j], fU, fD);
+                const double q = lap_node<N, ISO>(k, sl, p, j, i, fR[j], fL[j], fU, fD);
                 const double wq = k.w[j] * q;
                 a[0] = fmx(-wq, p[j * N + i], a[0]);
                 a[1] = fmx(wq, q, a[1]);
@@ -312,7 +318,7 @@ __device__ __forceinline__ void cg_step_body(
     // when r is no longer held: p_{k-1} is read again, and p_{k-2} where p_k is
     // stored
     if (store) {
-        if (par == 0 && !first) add_to_x<N>(x, pout, pin, self, alpha, s.alpha_prev);
+        if (par == 0 && !first) add_to_x<N>(x, pout, pin, self, ax, ax_prev);
         st_l64<N>(pout, self, p);
     }
 #pragma unroll

@@ -9,12 +9,12 @@ namespace dgk {
 
 template <int N, int WV, bool ISO>
 __global__ __launch_bounds__(64 * WV, N == 4 ? 4 : 1) void k_cg_step(
-    Geom g, int tilesX, int nblocks, OpConst<double> k, int par, const double* __restrict__ rin,
+    Geom g, int tilesX, int nblocks, OpConst<double> k, LapScale sl, int par, const double* __restrict__ rin,
     double* __restrict__ rout, const double* __restrict__ pin, double* __restrict__ pout,
     double* __restrict__ x, const CgScalars* __restrict__ sc_in, CgScalars* __restrict__ sc_out,
     const double* __restrict__ part_in, double* part_out, unsigned* counter) {
     __shared__ StepLds<N, WV> lds;
-    cg_step_body<N, WV, ISO>(blockIdx.x, g, tilesX, nblocks, k, par, rin, rout, pin, pout, x,
+    cg_step_body<N, WV, ISO>(blockIdx.x, g, tilesX, nblocks, k, sl, par, rin, rout, pin, pout, x,
                              sc_in, sc_out, part_in, part_out, counter, lds);
 }
 
@@ -55,7 +55,7 @@ hipError_t launch_cg_step(const Geom& g, const OpConst<double>& k, int par, cons
     DG_DISPATCH_NW(g.n, L.wv,                                                                  \
                    hipExtLaunchKernelGGL((k_cg_step<NN, WW, ISO>), dim3(L.nblocks),            \
                                          dim3(64 * WW), 0, s, start, stop, 0, g, L.tilesX,     \
-                                         L.nblocks, k, par, rin, rout, pin, pout, v.x,         \
+                                         L.nblocks, k, v.scale, par, rin, rout, pin, pout, v.x,      \
                                          (const CgScalars*)v.sc[par], v.sc[1 - par], part_in,  \
                                          part_out, counter))
     if (k.ihx == k.ihy) {

@@ -70,6 +70,13 @@ struct OpConst {
     double wq;                // hx * hy / 4: node weight = wq * w_i * w_j
 };
 
+// 1/hx^2 and 1/hy^2 times `unit`, the power of two that brings the entries of
+// Lap_h to about one.
+struct LapScale {
+    double x, y, unit;
+};
+LapScale lap_scale(int n, const OpConst<double>& k);
+
 // Default tile heights in waves: cell-per-lane tiles of 64 x 8 cells,
 // bracket tiles of 8 rows (the tuner may pick 4 / 16 and 16).
 constexpr int kCellWavesDefault = 8;

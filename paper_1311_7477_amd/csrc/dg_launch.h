@@ -64,6 +64,7 @@ hipError_t launch_cg_res(const Geom& g, const OpConst<double>& k, S* r, S* p0, S
 struct StepBuffers {
     double *x, *r0, *r1, *p0, *p1;
     CgScalars* sc[2];
+    LapScale scale;
     double* part;       // 2 step_part_stride(max_blocks) doubles
     int max_blocks;     // step_max_blocks
 };

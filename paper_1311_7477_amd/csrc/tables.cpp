@@ -192,4 +192,15 @@ void ldg_axis(const HostTables& t, double h, bool periodic, AxisLdg* out) {
     }
 }
 
+LapScale lap_scale(int n, const OpConst<double>& k) {
+    double m = 0.0;
+    for (int i = 0; i < n * n; ++i) {
+        m = std::fmax(m, std::fabs(k.L0x[i]) * k.ihx2);
+        m = std::fmax(m, std::fabs(k.L0y[i]) * k.ihy2);
+    }
+    const int e = m > 0.0 && std::isfinite(m) ? std::ilogb(m) : 0;
+    const double unit = std::ldexp(1.0, e < -1000 ? 1000 : (e > 1000 ? -1000 : -e));
+    return LapScale{k.ihx2 * unit, k.ihy2 * unit, unit};
+}
+
 }  // namespace dgk

@@ -33,7 +33,7 @@ int time_cg(dg_grid* g, const double* omega, dg_workspace* ws, int reps, hipEven
         e = launch_cg_init(geom, g->k64, omega, nullptr, nullptr, 0.0, 0.0, g->area, ws->x, ws->r,
                            ws->d, s);
     const StepBuffers v{ws->x, ws->r, ws->s1, ws->p0, ws->p1, {ws->d.sc, ws->d.sc + 1},
-                        ws->step_part, ws->step_max_blocks};
+                        g->scale, ws->step_part, ws->step_max_blocks};
     int par = 0;
     for (int i = 0; e == hipSuccess && i < 2; ++i, par ^= 1)
         e = launch_cg_step(geom, g->k64, par, v, ws->d.counters, s);
