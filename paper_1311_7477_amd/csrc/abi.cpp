@@ -216,14 +216,14 @@ int cg_loop(int total, int chunk, const CgScalars* sc, dg_workspace* ws, hipStre
 // The plain FP64 CG of a periodic grid, one launch per iteration.  A launch
 // evaluates the residual of the one before it, so the launch after the last
 // iteration allowed finds the solve stopped: max_iter + 2 launches, rounded up
-// to an even count (after which sc[0] is the newest).
+// to an even count (after which sc[0] is the newest), or none for max_iter = 0.
 int cg_steps(const dg_grid* g, const double* omega, const dg_cg_opts& o, dg_workspace* ws,
              hipStream_t s, CgScalars* fin) {
     // the second residual takes the RK field that does not hold the input
     StepBuffers v{ws->x, ws->r, omega == ws->s1 ? ws->s2 : ws->s1, ws->p0, ws->p1,
                   {ws->d.sc, ws->d.sc + 1}, g->scale, ws->step_part, ws->step_max_blocks};
     const int most = o.max_iter < (1 << 30) ? o.max_iter : (1 << 30);
-    const int total = (most + 3) & ~1;
+    const int total = most > 0 ? (most + 3) & ~1 : 0;
     const int every = o.check_every > 0 ? o.check_every : 32;
     const int chunk = every < total ? (every + 1) & ~1 : total;
     int round = -1;

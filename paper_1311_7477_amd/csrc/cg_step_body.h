@@ -178,6 +178,13 @@ __device__ __forceinline__ void cg_step_body(
     const int G = (g.nx + 63) / 64;
     const CellRef self = cell_ref<N>(g, G, gx, gy);
 
+    // A launch queued after the solve has stopped has nothing to do.  More blocks
+    // than are summed directly find that out first; else they would read all of r
+    // and p before (n = 4, 1448^2: 100 us for each of up to 64 such launches)
+    if (nblocks > kStepDirect && sc_in->done) {
+        if (b == 0 && threadIdx.x == 0) *sc_out = *sc_in;
+        return;
+    }
     // the previous launch's block sums and the cells' values, asked for before
     // anything is known of the solve's state (at the first iteration p, h and
     // the sums are not used)
