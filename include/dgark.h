@@ -173,9 +173,8 @@ int  dg_grid_tables(const dg_grid* grid, double* out, int len);
 /* Tile shapes of the grid's stencil launches: the cell-per-lane kernels
  * (Laplacian, CG) use tiles of 64 x cw cells, cw in {4, 8, 16}; the fused
  * bracket kernel tiles of rw rows, rw in {8, 16} (default 8 and 8; larger
- * periodic grids walk strips of cells instead, whatever rw).  The iteration
- * kernel of the plain periodic CG takes tiles of cw rows that store the inner
- * 60 x (cw - 2) cells, of 4 or 8 rows at cw = 8 by the number of tiles.  Taller
+ * periodic grids walk strips of cells instead, whatever rw; the iteration kernel
+ * of the plain periodic CG has tiles of its own, whatever cw).  Taller
  * tiles re-read fewer halo rows but hold more registers and LDS per
  * workgroup.  The shapes change the reduction order and hence the last bits
  * of CG results; set them before using the grid (a batch copies them when an

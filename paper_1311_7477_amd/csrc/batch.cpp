@@ -21,11 +21,12 @@ namespace {
 
 enum ListKind { kCell = 0, kStep, kRow, kPwRows, kPwCells, kPwElems, kListCount };
 
-// Launch groups: one per (polynomial order, cell tile height, CG tile height,
-// bracket tile height); every kernel kind of a group is one fused launch.
+// Launch groups: one per (polynomial order, cell tile height, CG tile height and
+// whether its rows wrap, bracket tile height); every kernel kind of a group is one fused launch.
 constexpr int kCellShapes[3] = {4, 8, 16};
 constexpr int kRowShapes[2] = {8, 16};
-constexpr int kShapes = 18;
+constexpr int kStepShapes[2] = {4, 8};
+constexpr int kShapes = 24;
 constexpr int kGroups = kMaxN * kShapes;
 using GroupMask = std::bitset<kGroups>;
 
@@ -36,16 +37,19 @@ int cell_shape(int waves) { return waves == 4 ? 0 : (waves == 8 ? 1 : 2); }
 
 int group_of(const Geom& g) {
     const int ri = g.rw == 8 ? 0 : 1;
-    return (g.n - 1) * kShapes + (cell_shape(g.cw) * 3 + cell_shape(step_waves(g))) * 2 + ri;
+    const int si = (step_waves(g) == 4 ? 0 : 1) + (step_wraps(g) ? 2 : 0);
+    return (g.n - 1) * kShapes + (cell_shape(g.cw) * 4 + si) * 2 + ri;
 }
 
 struct GroupShape {
-    int n, cw, sw, rw;
+    int n, cw, sw;
+    bool wrap;
+    int rw;
 };
 
 GroupShape shape_of(int gi) {
     const int n = gi / kShapes + 1, s = gi % kShapes;
-    return GroupShape{n, kCellShapes[s / 6], kCellShapes[s / 2 % 3], kRowShapes[s % 2]};
+    return GroupShape{n, kCellShapes[s / 8], kStepShapes[s / 2 % 2], s / 4 % 2 != 0, kRowShapes[s % 2]};
 }
 
 struct Slot {
@@ -173,10 +177,10 @@ int enqueue_setup(dg_batch* b, hipStream_t s) {
     for (int gi = 0; gi < kGroups; ++gi) {
         if (!b->group_mask[gi]) continue;
         const GroupShape q = shape_of(gi);
-        hipError_t e = launch_batch(q.n, q.cw, q.sw, q.rw, BatchKernel::Mean, b->d_inst,
+        hipError_t e = launch_batch(q.n, q.cw, q.sw, q.wrap, q.rw, BatchKernel::Mean, b->d_inst,
                                     list_of(b, gi, kPwRows), grid_of(b, gi, kPwRows), s);
         if (e == hipSuccess)
-            e = launch_batch(q.n, q.cw, q.sw, q.rw, BatchKernel::Init, b->d_inst,
+            e = launch_batch(q.n, q.cw, q.sw, q.wrap, q.rw, BatchKernel::Init, b->d_inst,
                              list_of(b, gi, kCell), grid_of(b, gi, kCell), s);
         if (e != hipSuccess) return hip_fail(e, "batch setup launch");
     }
@@ -189,7 +193,7 @@ int enqueue_setup(dg_batch* b, hipStream_t s) {
 int enqueue_chunk(dg_batch* b, int gi, hipStream_t s) {
     const GroupShape q = shape_of(gi);
     for (int i = 0; i < b->chunk; ++i) {
-        hipError_t e = launch_batch(q.n, q.cw, q.sw, q.rw,
+        hipError_t e = launch_batch(q.n, q.cw, q.sw, q.wrap, q.rw,
                                     i & 1 ? BatchKernel::StepOdd : BatchKernel::StepEven,
                                     b->d_inst, list_of(b, gi, kStep), grid_of(b, gi, kStep), s);
         if (e != hipSuccess) return hip_fail(e, "batch CG launch");
@@ -201,13 +205,13 @@ int enqueue_finish(dg_batch* b, hipStream_t s) {
     for (int gi = 0; gi < kGroups; ++gi) {
         if (!b->group_mask[gi]) continue;
         const GroupShape q = shape_of(gi);
-        hipError_t e = launch_batch(q.n, q.cw, q.sw, q.rw, BatchKernel::Finish, b->d_inst,
+        hipError_t e = launch_batch(q.n, q.cw, q.sw, q.wrap, q.rw, BatchKernel::Finish, b->d_inst,
                                     list_of(b, gi, kPwCells), grid_of(b, gi, kPwCells), s);
         if (e == hipSuccess)
-            e = launch_batch(q.n, q.cw, q.sw, q.rw, BatchKernel::SubMean, b->d_inst,
+            e = launch_batch(q.n, q.cw, q.sw, q.wrap, q.rw, BatchKernel::SubMean, b->d_inst,
                              list_of(b, gi, kPwElems), grid_of(b, gi, kPwElems), s);
         if (e == hipSuccess)
-            e = launch_batch(q.n, q.cw, q.sw, q.rw, BatchKernel::Rhs, b->d_inst,
+            e = launch_batch(q.n, q.cw, q.sw, q.wrap, q.rw, BatchKernel::Rhs, b->d_inst,
                              list_of(b, gi, kRow), grid_of(b, gi, kRow), s);
         if (e != hipSuccess) return hip_fail(e, "batch finish launch");
     }

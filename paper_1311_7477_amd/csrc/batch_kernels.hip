@@ -47,12 +47,12 @@ __global__ __launch_bounds__(64 * WV, (N <= 4 ? 4 : 1)) void kb_cg_init(const Ba
     }
 }
 
-template <int N, int WV, int PAR>
+template <int N, int WV, bool WRAP, int PAR>
 __global__ __launch_bounds__(64 * WV, (N <= 4 ? 4 : 1)) void kb_cg_step(const BatchInst* __restrict__ inst, ItemList list) {
     __shared__ StepLds<N, WV> lds;
     DG_FOR_ITEMS(list) {
         const size_t stride = step_part_stride(B.step_max_blocks);
-        cg_step_body<N, WV, false>(item_.b, B.g, B.step_tilesX, B.step_nblocks, B.k, B.scale, PAR,
+        cg_step_body<N, WV, false, WRAP>(item_.b, B.g, B.step_tilesX, B.step_nblocks, B.k, B.scale, PAR,
                                    PAR ? B.r1 : B.r, PAR ? B.r : B.r1, PAR ? B.p1 : B.p0,
                                    PAR ? B.p0 : B.p1, B.x, PAR ? B.sc1 : B.sc,
                                    PAR ? B.sc : B.sc1, B.step_part + PAR * stride,
@@ -111,7 +111,7 @@ void fill_batch_geometry(BatchInst& b) {
     b.nb_elems = pw_blocks(b.elems, pointwise_block_cap());
 }
 
-hipError_t launch_batch(int n, int cw, int sw, int rw, BatchKernel kind, const BatchInst* inst,
+hipError_t launch_batch(int n, int cw, int sw, bool wrap, int rw, BatchKernel kind, const BatchInst* inst,
                         const ItemList& list, int grid, hipStream_t s) {
     const dim3 pw(kPwThreads);
     switch (kind) {
@@ -123,12 +123,22 @@ hipError_t launch_batch(int n, int cw, int sw, int rw, BatchKernel kind, const B
                                                      dim3(64 * WW), 0, s, inst, list));
             break;
         case BatchKernel::StepEven:
-            DG_DISPATCH_NW(n, sw, hipLaunchKernelGGL((kb_cg_step<NN, WW, 0>), dim3(grid),
-                                                     dim3(64 * WW), 0, s, inst, list));
-            break;
         case BatchKernel::StepOdd:
-            DG_DISPATCH_NW(n, sw, hipLaunchKernelGGL((kb_cg_step<NN, WW, 1>), dim3(grid),
-                                                     dim3(64 * WW), 0, s, inst, list));
+#define DG_STEP(WRAP, PAR)                                                                     \
+    DG_DISPATCH_NS(n, sw, hipLaunchKernelGGL((kb_cg_step<NN, WW, WRAP, PAR>), dim3(grid),      \
+                                             dim3(64 * WW), 0, s, inst, list))
+            if (kind == BatchKernel::StepEven) {
+                if (wrap) {
+                    DG_STEP(true, 0);
+                } else {
+                    DG_STEP(false, 0);
+                }
+            } else if (wrap) {
+                DG_STEP(true, 1);
+            } else {
+                DG_STEP(false, 1);
+            }
+#undef DG_STEP
             break;
         case BatchKernel::Finish:
             DG_DISPATCH_N(n, hipLaunchKernelGGL((kb_cg_finish<NN>), dim3(grid), pw, 0, s, inst,

@@ -26,7 +26,7 @@
 //
 // r_k and p_k are needed one cell beyond the cells whose A p_k is summed, so a
 // tile is 64 x WV cells of which the inner 60 x (WV - 2) are summed and
-// stored; the rest is formed again by the neighbouring tiles (the two outer
+// stored (all 64 lanes on rows of 61 to 64 cells, step_rim); the rest is formed again by the neighbouring tiles (the two outer
 // lanes on each side have no valid neighbour and only feed the next ones; the
 // face scalars beyond the first and last cell row are taken from a row loaded
 // for them).  r and p are double-buffered.  Leaving face scalars for the
@@ -52,11 +52,12 @@ __host__ __device__ constexpr size_t step_part_stride(int nblocks) {
     return (size_t)kStepSums * (nblocks + kTicketGroups);
 }
 
-// Tiles of one launch: 64 x wv cells, the inner 60 x (wv - 2) stored.
+// Tiles of one launch: 64 x wv cells, of which (64 - 2 rim) x (wv - 2) are stored.
 struct StepLaunch {
     int wv, tilesX, tilesY, nblocks;
     __host__ __device__ StepLaunch(const Geom& g, int waves) : wv(waves) {
-        tilesX = (g.nx + 59) / 60;
+        const int w = 64 - 2 * step_rim(g);
+        tilesX = (g.nx + w - 1) / w;
         tilesY = (g.ny + wv - 3) / (wv - 2);
         nblocks = tilesX * tilesY;
     }
@@ -155,10 +156,12 @@ __device__ __forceinline__ void add_to_x(double* __restrict__ x, const double* p
     }
 }
 
+// kWrap: rows of 61 to 63 cells, which end within the wave (a template parameter:
+// tested for at run time, all other rows take 8 to 30% longer at n = 5).
 // par: the launch's parity, that of the iteration while the solve runs.  The
 // scalars and block sums written by the launch before are read from sc_in and
 // part_in, this launch's go to sc_out and part_out.
-template <int N, int WV, bool ISO>
+template <int N, int WV, bool ISO, bool kWrap>
 __device__ __forceinline__ void cg_step_body(
     int b, Geom g, int tilesX, int nblocks, const OpConst<double>& k, const LapScale& sl, int par,
     const double* __restrict__ rin, double* __restrict__ rout, const double* __restrict__ pin,
@@ -169,12 +172,15 @@ __device__ __forceinline__ void cg_step_body(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int t = xcd_tile(b, nblocks);
     const int ty = t / tilesX, tx = t - ty * tilesX;
-    const int cx = tx * 60 + lane - 2, cy = ty * (WV - 2) + wave - 1;
+    const int rim = kWrap ? 0 : step_rim(g);
+    const int cx = tx * (64 - 2 * rim) + lane - rim, cy = ty * (WV - 2) + wave - 1;
     const bool inner = wave > 0 && wave < WV - 1 && cy < g.ny;        // wave-uniform
-    const bool store = inner && lane > 1 && lane < 62 && cx < g.nx;
-    int gx = cx < 0 ? cx + 2 * g.nx : cx;                             // cx >= -2, nx >= 1
+    const bool store = inner && lane >= rim && lane < 64 - rim && cx < g.nx;
+    // past the rims the outermost cell again, which its neighbours have read
+    const int cxr = cx < g.nx + 1 ? cx : g.nx + 1, cyr = cy < g.ny + 1 ? cy : g.ny + 1;
+    int gx = cxr < 0 ? cxr + 2 * g.nx : cxr;                          // cx >= -2, nx >= 1
     if (gx >= g.nx) gx %= g.nx;
-    const int gy = (cy + g.ny) % g.ny;
+    const int gy = (cyr + g.ny) % g.ny;
     const int G = (g.nx + 63) / 64;
     const CellRef self = cell_ref<N>(g, G, gx, gy);
 
@@ -275,8 +281,14 @@ __device__ __forceinline__ void cg_step_body(
         }
 #pragma unroll
         for (int j = 0; j < N; ++j) {
-            fR[j] = lane_next(xdot<N>(u, j, k.lR));
-            fL[j] = lane_prev(xdot<N>(u, j, k.lLx));
+            const double toL = xdot<N>(u, j, k.lR), toR = xdot<N>(u, j, k.lLx);
+            fR[j] = lane_next(toL);
+            fL[j] = lane_prev(toR);
+            if (kWrap) {
+                const double first = read_lane(toL, 0), last = read_lane(toR, g.nx - 1);
+                if (lane == g.nx - 1) fR[j] = first;
+                if (lane == 0) fL[j] = last;
+            }
         }
     };
 

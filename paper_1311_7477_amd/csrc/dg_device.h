@@ -176,6 +176,14 @@ __device__ bool reduce_last(double (&v)[NV], double* partials,
         default: return hipErrorInvalidValue;                              \
     }
 
+// The same for the CG iteration kernel (WW, 4 or 8).
+#define DG_DISPATCH_NS(n, w, ...)                                          \
+    switch (w) {                                                           \
+        case 4: { constexpr int WW = 4; DG_DISPATCH_N(n, __VA_ARGS__); } break;   \
+        case 8: { constexpr int WW = 8; DG_DISPATCH_N(n, __VA_ARGS__); } break;   \
+        default: return hipErrorInvalidValue;                              \
+    }
+
 // Dispatch on n (NN) and the bracket kernel's tile height (WW, 8 or 16).
 #define DG_DISPATCH_NR(n, w, ...)                                          \
     switch (w) {                                                           \

@@ -93,6 +93,13 @@ struct Geom {
     int bcx, bcy;     // 1: homogeneous Dirichlet along x / y
 };
 
+// Lanes on each side of a CG iteration kernel's tile that store nothing: none where a
+// row of cells fits one wave and would not leave room for them; its ends are
+// neighbours then (n = 5, 62 x 8192: two tiles a row 260 us per iteration, one 160).
+constexpr int step_rim(const Geom& g) { return g.nx > 60 && g.nx <= 64 ? 0 : 2; }
+// Rows that end within the wave (at 64 cells a rotation of the wave closes them).
+constexpr bool step_wraps(const Geom& g) { return g.nx > 60 && g.nx < 64; }
+
 // Bracket / right-hand-side kernel parameters:
 //   J = scale * (c0 J++ + Dx(c1 f Dy g - c2 Dy f g) + Dy(c2 Dx f g - c1 f Dx g))
 // and, for an RK stage, out = a * w_n + b * (g + dt * (-J + D Lap_h g)), or
