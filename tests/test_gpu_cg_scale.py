@@ -9,10 +9,9 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-# nodes, weights and the 2 pi of the domain: |omega| <= 8, W <= 1, the entries of
-# A up to 2^16 (n = 4, 24 cells): <p, A p> stays under 2^1024 up to scales of
-# about 2^(1024 - 16) / 2 less a few bits for the sum over the nodes
-@pytest.mark.parametrize("n,N,power", [(1, 40, 490), (3, 24, 490), (4, 24, 490), (3, 24, -300)])
+# |omega| < 2^3 and W < 2^3 summed over the domain: <r, r> stays under 2^1024 up to
+# scales of 2^507; <A p, A p> itself would pass it from 2^503 (n = 1) and 2^499 on.
+@pytest.mark.parametrize("n,N,power", [(1, 40, 504), (3, 24, 502), (4, 24, 502), (3, 24, -300)])
 def test_scaled_vorticity(n, N, power):
     from paper_1311_7477_amd import dg
     print(f"cg scale n={n} N={N} 2^{power}", flush=True)
@@ -27,11 +26,10 @@ def test_scaled_vorticity(n, N, power):
     assert out[0][0] == out[1][0] and torch.equal(out[0][1], out[1][1])
     w1, w2 = w.clone(), w * 2.0 ** power
     batch = dg.Batch(2)
-    # (D = 0, dt = 0: the solves alone)
+    # (D = 0, dt = 0; the first solve alone: the bracket of the scaled fields overflows)
     a, b = batch.attach(grid, w1, 0.0, 0.0), batch.attach(grid, w2, 0.0, 0.0)
-    iters, ok = batch.rk_step(dg.cg_opts(rtol=1e-10))
-    assert iters[a][0] == iters[b][0] == out[0][0]
-    assert iters[a][0] > 10 and ok
+    iters, _ = batch.rk_step(dg.cg_opts(rtol=1e-10, max_iter=2000))
+    assert iters[a][0] == iters[b][0] == out[0][0] > 10
 
 
 @pytest.mark.parametrize("power", [-200, 200])
