@@ -186,8 +186,10 @@ int  dg_grid_tiles(const dg_grid* grid, int* cw, int* rw);
  * cell tile height and `reps` fused bracket evaluations for each bracket tile
  * height on this grid, from the caller's field omega (device, canonical; its
  * mean-free part must be nonzero), and set the fastest shapes in the grid.
- * ms_out5 (host, optional): mean ms per CG iteration for cw = 4, 8, 16 and
- * per bracket for rw = 8, 16.  Allocates and frees a temporary workspace;
+ * ms_out5 (host, optional): mean ms per CG iteration (the two kernels that take
+ * cell tiles: those of preconditioned solves and of FP32-stored vectors) for cw =
+ * 4, 8, 16 and per bracket for rw = 8, 16 (the same time twice, and rw = 8, where
+ * strips are walked).  Allocates and frees a temporary workspace;
  * synchronises the stream.  Not thread-safe with other users of the grid. */
 int  dg_grid_tune(dg_grid* grid, const double* omega, int reps, double* ms_out5,
                   void* stream);

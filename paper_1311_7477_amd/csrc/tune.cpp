@@ -21,9 +21,10 @@ constexpr int kRowCandidates[2] = {8, 16};
 bool valid_cw(int cw) { return cw == 4 || cw == 8 || cw == 16; }
 bool valid_rw(int rw) { return rw == 8 || rw == 16; }
 
-// Mean milliseconds of one CG iteration with
-// the grid's current cell tile, from a fresh CG setup on omega that cannot
-// converge (tol = 0).  Returns a negative status on error.
+// Mean milliseconds of one CG iteration of the two-kernel form (direction, then
+// residual update) with the grid's current cell tile, from a fresh CG setup on
+// omega that cannot converge (tol = 0).  The plain periodic solve's own kernel has
+// tiles that do not follow the cell tile.  Returns a negative status on error.
 int time_cg(dg_grid* g, const double* omega, dg_workspace* ws, int reps, hipEvent_t e0,
             hipEvent_t e1, hipStream_t s, float* ms) {
     const Geom& geom = g->geom;
@@ -32,20 +33,20 @@ int time_cg(dg_grid* g, const double* omega, dg_workspace* ws, int reps, hipEven
     if (e == hipSuccess)
         e = launch_cg_init(geom, g->k64, omega, nullptr, nullptr, 0.0, 0.0, g->area, ws->x, ws->r,
                            ws->d, s);
-    const StepBuffers v{ws->x, ws->r, ws->s1, ws->p0, ws->p1, {ws->d.sc, ws->d.sc + 1},
-                        g->scale, ws->step_part, ws->step_max_blocks};
-    int par = 0;
-    for (int i = 0; e == hipSuccess && i < 2; ++i, par ^= 1)
-        e = launch_cg_step(geom, g->k64, par, v, ws->d.counters, s);
+    auto iterate = [&](int count) {
+        for (int i = 0; e == hipSuccess && i < count; ++i)
+            e = launch_cg_iter<double>(geom, g->k64, ws->x, ws->r, ws->p0, ws->p1, ws->d.sc,
+                                       ws->d, s);
+    };
+    iterate(2);
     if (e == hipSuccess) e = hipEventRecord(e0, s);
-    for (int i = 0; e == hipSuccess && i < reps; ++i, par ^= 1)
-        e = launch_cg_step(geom, g->k64, par, v, ws->d.counters, s);
+    iterate(reps);
     if (e == hipSuccess) e = hipEventRecord(e1, s);
     if (e == hipSuccess) e = hipEventSynchronize(e1);
     if (e == hipSuccess) e = hipEventElapsedTime(ms, e0, e1);
     if (e != hipSuccess) return hip_fail(e, "tuning CG launch");
     CgScalars h;
-    HIP_TRY(hipMemcpy(&h, ws->d.sc + par, sizeof h, hipMemcpyDeviceToHost));
+    HIP_TRY(hipMemcpy(&h, ws->d.sc, sizeof h, hipMemcpyDeviceToHost));
     if (h.done)
         return fail(DG_E_INVAL, "tuning needs an omega whose mean-free part is nonzero "
                     "(the CG stopped after %d iterations)", h.iter);
@@ -123,8 +124,14 @@ int dg_grid_tune(dg_grid* g, const double* omega, int reps, double* ms_out5, voi
         hipError_t e = launch_laplace(g->geom, g->k64, omega, ws->s2, s);
         if (e != hipSuccess) rc = hip_fail(e, "tuning Laplacian launch");
     }
+    // (strips take no notice of rw: timed once, and the default stays)
+    const bool strips = rhs_strips(g->geom);
     for (int i = 0; rc == DG_OK && i < 2; ++i) {
         g->geom.rw = kRowCandidates[i];
+        if (strips && i > 0) {
+            t_row[i] = t_row[0];
+            continue;
+        }
         rc = time_rhs(g, omega, ws, reps, e0, e1, s, &t_row[i]);
     }
     if (rc == DG_OK) {
