@@ -228,10 +228,11 @@ int cg_steps(const dg_grid* g, const double* omega, const dg_cg_opts& o, dg_work
     const int chunk = every < total ? (every + 1) & ~1 : total;
     int round = -1;
     return cg_loop(total, chunk, ws->d.sc, ws, s, fin, [&](int launch, int i, int slot) {
-        // the sampled launch alternates between the first and the second of a
-        // chunk, so that launches with and without the x update count alike
+        // the sampled launch alternates between the second and the first of a
+        // chunk, so that launches without and with the x update count alike; the
+        // very first one, which applies the operator once, is never sampled
         if (i == 0) ++round;
-        const bool timed = ws->prof_on && i == (round & 1);
+        const bool timed = ws->prof_on && i == (~round & 1);
         hipError_t e = launch_cg_step(g->geom, g->k64, launch & 1, v, ws->d.counters, s,
                                       timed ? ws->pev[slot][0] : nullptr,
                                       timed ? ws->pev[slot][1] : nullptr);
