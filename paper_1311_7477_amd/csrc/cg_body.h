@@ -605,7 +605,7 @@ __device__ __forceinline__ void cg_init_body(
 template <int N, class S, int WV, bool DIR = false, bool ISO = false>
 __device__ __forceinline__ void cg_dir_body(
     int b, Geom g, int tilesX, int nblocks, const OpConst<double>& k,
-    const S* r, S* p0, S* p1, double* __restrict__ x,
+    const S* __restrict__ r, S* p0, S* p1, double* __restrict__ x,
     CgScalars* sc, unsigned* counter, double* partials,
     YFaces<N, double, WV>& lds) {
     if (sc->done) return;

@@ -35,7 +35,7 @@ __global__ __launch_bounds__(64 * WV) void k_cg_init(
 // lane the residual kernel then spills.
 template <int N, class S, int WV, bool DIR, bool ISO>
 __global__ __launch_bounds__(64 * WV, (N == 4 && !DIR) ? 4 : 1) void k_cg_dir(
-    Geom g, int tilesX, int nblocks, OpConst<double> k, const S* r,
+    Geom g, int tilesX, int nblocks, OpConst<double> k, const S* __restrict__ r,
     S* p0, S* p1, double* __restrict__ x, CgScalars* sc, unsigned* counter,
     double* partials) {
     __shared__ YFaces<N, double, WV> lds;
