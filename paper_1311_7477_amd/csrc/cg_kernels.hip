@@ -38,7 +38,7 @@ __global__ __launch_bounds__(64 * WV, (N == 4 && !DIR) ? 4 : 1) void k_cg_dir(
     Geom g, int tilesX, int nblocks, OpConst<double> k, const S* __restrict__ r,
     S* p0, S* p1, double* __restrict__ x, CgScalars* sc, unsigned* counter,
     double* partials) {
-    __shared__ YFaces<N, double, WV> lds;
+    __shared__ PairFaces<N, double, WV> lds;
     cg_dir_body<N, S, WV, DIR, ISO>(blockIdx.x, g, tilesX, nblocks, k, r, p0, p1, x, sc,
                                counter, partials, lds);
 }
@@ -47,7 +47,7 @@ template <int N, class S, int WV, bool DIR, bool ISO>
 __global__ __launch_bounds__(64 * WV, (N == 4 && !DIR) ? 4 : 1) void k_cg_res(
     Geom g, int tilesX, int nblocks, OpConst<double> k, const S* p0, const S* p1,
     S* __restrict__ r, CgScalars* sc, unsigned* counter, double* partials) {
-    __shared__ YFaces<N, double, WV> lds;
+    __shared__ PairFaces<N, double, WV> lds;
     cg_res_body<N, S, WV, DIR, ISO>(blockIdx.x, g, tilesX, nblocks, k, p0, p1, r, sc, counter,
                                partials, lds);
 }
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(64 * WV) void k_mixed_replace(
     const double* __restrict__ omega, const double* __restrict__ x,
     const float* __restrict__ q0, const float* __restrict__ q1,
     float* __restrict__ r32, CgScalars* sc, unsigned* counter, double* partials) {
-    __shared__ YFaces<N, double, WV> lds;
+    __shared__ PairFaces<N, double, WV> lds;
     mixed_replace_body<N, WV, ISO>(blockIdx.x, g, tilesX, nblocks, k, omega, x, q0, q1, r32,
                           sc, counter, partials, lds);
 }
