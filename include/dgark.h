@@ -171,7 +171,7 @@ size_t dg_field_elems(const dg_grid* grid);
 int  dg_grid_tables(const dg_grid* grid, double* out, int len);
 
 /* Tile shapes of the grid's stencil launches: the cell-per-lane kernels
- * (Laplacian, CG) use tiles of 64 x cw cells, cw in {4, 8, 16}; the fused
+ * (Laplacian, CG) use tiles of 64 x cw cells, cw in {4, 8, 16} (16 as 8 at n = 5); the fused
  * bracket kernel tiles of rw rows, rw in {8, 16} (default 8 and 8; larger
  * periodic grids walk strips of cells instead, whatever rw; the iteration kernel
  * of the plain periodic CG has tiles of its own, whatever cw).  Taller

@@ -119,8 +119,10 @@ hipError_t launch_batch(int n, int cw, int sw, bool wrap, int rw, BatchKernel ki
             DG_DISPATCH_N(n, hipLaunchKernelGGL((kb_cg_mean<NN>), dim3(grid), pw, 0, s, inst, list));
             break;
         case BatchKernel::Init:
-            DG_DISPATCH_NW(n, cw, hipLaunchKernelGGL((kb_cg_init<NN, WW>), dim3(grid),
-                                                     dim3(64 * WW), 0, s, inst, list));
+            DG_DISPATCH_NW(n, cw, hipLaunchKernelGGL((kb_cg_init<NN, cell_waves(NN, WW)>),
+                                                     dim3(grid),
+                                                     dim3(64 * cell_waves(NN, WW)), 0, s, inst,
+                                                     list));
             break;
         case BatchKernel::StepEven:
         case BatchKernel::StepOdd:

@@ -885,7 +885,8 @@ __device__ __forceinline__ void mixed_replace_body(
 // Tiles of one cell-per-lane launch on a grid.
 struct CellLaunch {
     int tilesX, tilesY, nblocks;
-    __host__ __device__ explicit CellLaunch(const Geom& g) : CellLaunch(g, g.cw) {}
+    __host__ __device__ explicit CellLaunch(const Geom& g)
+        : CellLaunch(g, cell_waves(g.n, g.cw)) {}
     __host__ __device__ CellLaunch(const Geom& g, int cw) {
         tilesX = (g.nx + 63) / 64;
         tilesY = (g.ny + cw - 1) / cw;

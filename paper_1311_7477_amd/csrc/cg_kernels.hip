@@ -131,15 +131,15 @@ hipError_t launch_cg_init(const Geom& g, const OpConst<double>& k,
         return hipGetLastError();
     }
     if (iso(g, k)) {
-        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_cg_init<NN, WW, false, true>),
+        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_cg_init<NN, cell_waves(NN, WW), false, true>),
                                                      dim3(L.nblocks),
-                                              dim3(64 * WW), 0, s, g, L.tilesX,
+                                              dim3(64 * cell_waves(NN, WW)), 0, s, g, L.tilesX,
                                               L.nblocks, k, omega, pa, pb, ca, cb, inv_area, x, r,
                                               d.sc, d.counters + kCntInit * kCntStride, d.partials, img));
     } else {
-        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_cg_init<NN, WW, false, false>),
+        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_cg_init<NN, cell_waves(NN, WW), false, false>),
                                                      dim3(L.nblocks),
-                                              dim3(64 * WW), 0, s, g, L.tilesX,
+                                              dim3(64 * cell_waves(NN, WW)), 0, s, g, L.tilesX,
                                               L.nblocks, k, omega, pa, pb, ca, cb, inv_area, x, r,
                                               d.sc, d.counters + kCntInit * kCntStride, d.partials, img));
     }
@@ -171,15 +171,15 @@ hipError_t launch_cg_dir(const Geom& g, const OpConst<double>& k, double* x, S* 
         return hipErrorInvalidValue;
     }
     if (iso(g, k)) {
-        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_cg_dir<NN, S, WW, false, true>),
+        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_cg_dir<NN, S, cell_waves(NN, WW), false, true>),
                                                      dim3(L.nblocks),
-                                              dim3(64 * WW), 0, s, g, L.tilesX,
+                                              dim3(64 * cell_waves(NN, WW)), 0, s, g, L.tilesX,
                                               L.nblocks, k, r, p0, p1, x, sc,
                                               d.counters + kCntDir * kCntStride, d.partials));
     } else {
-        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_cg_dir<NN, S, WW, false, false>),
+        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_cg_dir<NN, S, cell_waves(NN, WW), false, false>),
                                                      dim3(L.nblocks),
-                                              dim3(64 * WW), 0, s, g, L.tilesX,
+                                              dim3(64 * cell_waves(NN, WW)), 0, s, g, L.tilesX,
                                               L.nblocks, k, r, p0, p1, x, sc,
                                               d.counters + kCntDir * kCntStride, d.partials));
     }
@@ -211,15 +211,15 @@ hipError_t launch_cg_res(const Geom& g, const OpConst<double>& k, S* r, S* p0, S
         return hipErrorInvalidValue;
     }
     if (iso(g, k)) {
-        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_cg_res<NN, S, WW, false, true>),
+        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_cg_res<NN, S, cell_waves(NN, WW), false, true>),
                                                      dim3(L.nblocks),
-                                              dim3(64 * WW), 0, s, g, L.tilesX,
+                                              dim3(64 * cell_waves(NN, WW)), 0, s, g, L.tilesX,
                                               L.nblocks, k, p0, p1, r, sc,
                                               d.counters + kCntRes * kCntStride, d.partials));
     } else {
-        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_cg_res<NN, S, WW, false, false>),
+        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_cg_res<NN, S, cell_waves(NN, WW), false, false>),
                                                      dim3(L.nblocks),
-                                              dim3(64 * WW), 0, s, g, L.tilesX,
+                                              dim3(64 * cell_waves(NN, WW)), 0, s, g, L.tilesX,
                                               L.nblocks, k, p0, p1, r, sc,
                                               d.counters + kCntRes * kCntStride, d.partials));
     }
@@ -256,15 +256,15 @@ hipError_t launch_mixed_replace(const Geom& g, const OpConst<double>& k,
     CellLaunch L(g);
     if (dirichlet(g)) return hipErrorInvalidValue;
     if (iso(g, k)) {
-        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_mixed_replace<NN, WW, true>),
+        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_mixed_replace<NN, cell_waves(NN, WW), true>),
                                                      dim3(L.nblocks),
-                                              dim3(64 * WW), 0, s, g, L.tilesX,
+                                              dim3(64 * cell_waves(NN, WW)), 0, s, g, L.tilesX,
                                               L.nblocks, k, omega, x, q0, q1, r32,
                                               d.sc, d.counters + kCntDot * kCntStride, d.partials));
     } else {
-        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_mixed_replace<NN, WW, false>),
+        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_mixed_replace<NN, cell_waves(NN, WW), false>),
                                                      dim3(L.nblocks),
-                                              dim3(64 * WW), 0, s, g, L.tilesX,
+                                              dim3(64 * cell_waves(NN, WW)), 0, s, g, L.tilesX,
                                               L.nblocks, k, omega, x, q0, q1, r32,
                                               d.sc, d.counters + kCntDot * kCntStride, d.partials));
     }

@@ -93,6 +93,13 @@ struct Geom {
     int bcx, bcy;     // 1: homogeneous Dirichlet along x / y
 };
 
+// Waves per tile of the cell-per-lane kernels on a grid with cell tiles of cw waves.
+// At n = 5 a block of 16 waves has 128 registers a lane, and the kernels spilled 64 to
+// 500 bytes a lane and up to 180 scalar registers; a solve with FP32-stored vectors on
+// 1000 x 700 cells faulted in one of them.  Tiles of 8 do not spill and take less than
+// half the time (128^2, 64 iterations: 1.88 against 4.38 ms).
+constexpr int cell_waves(int n, int cw) { return n == 5 && cw == 16 ? 8 : cw; }
+
 // Lanes on each side of a CG iteration kernel's tile that store nothing: none where a
 // row of cells fits one wave and would not leave room for them; its ends are
 // neighbours then (n = 5, 62 x 8192: two tiles a row 260 us per iteration, one 160).

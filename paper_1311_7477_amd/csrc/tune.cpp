@@ -116,6 +116,11 @@ int dg_grid_tune(dg_grid* g, const double* omega, int reps, double* ms_out5, voi
     float t_cell[3] = {0, 0, 0}, t_row[2] = {0, 0};
     for (int i = 0; rc == DG_OK && i < 3; ++i) {
         g->geom.cw = kCellCandidates[i];
+        // (tiles of 16 that run as tiles of 8 are not timed again: 8 is kept)
+        if (cell_waves(g->geom.n, kCellCandidates[i]) != kCellCandidates[i]) {
+            t_cell[i] = t_cell[i - 1];
+            continue;
+        }
         rc = time_cg(g, omega, ws, reps, e0, e1, s, &t_cell[i]);
     }
     // the bracket's second argument: the derivative-rich field s2 = Lap_h omega

@@ -8,8 +8,8 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-# at n = 5 and few tiles the two-kernel iteration takes 21 us with cw = 4, 27 with 8
-# and 58 with 16; the one-kernel iteration, whose tiles do not follow cw, 10
+# at n = 5 and few tiles the two-kernel iteration takes 21 us with cw = 4 and 27 with 8
+# (16 runs as 8 there); the one-kernel iteration, whose tiles do not follow cw, 10
 def test_cell_tiles():
     from paper_1311_7477_amd import dg
     print("tune cell tiles", flush=True)
@@ -18,7 +18,7 @@ def test_cell_tiles():
     for _ in range(3):
         (cw, _rw), ms = grid.tune(w, reps=50)
         assert cw == 4
-        assert 1.1 * ms[0] < ms[1] and 1.1 * ms[1] < ms[2]
+        assert 1.1 * ms[0] < ms[1] == ms[2]
 
 
 # a grid walked by strips: one kernel whatever rw, which stays 8
