@@ -715,7 +715,6 @@ __device__ __forceinline__ void cg_dir_body(
         if (tot[0] > 0.0 && tot[0] == tot[0]) {
             sc->alpha_prev = alpha;
             sc->alpha = (kStoredLow<S> ? tot[NV - 1] : sc->rz) / tot[0];
-            if (!kStoredLow<S> && sc->precond) sc->mean_x += sc->alpha * sc->mean_p;
         } else {  // breakdown (or non-finite data): stop; x lacks
                   // alpha_{k-1} p_{k-1} (still in pin) if its update waited
             sc->done = 1;
@@ -757,6 +756,8 @@ __device__ __forceinline__ void cg_res_body(
         if (!sc->precond) {           // plain CG: z = r
             sc->beta = rrn / sc->rz;
             sc->rz = rrn;
+        } else if (!kStoredLow<S>) {
+            sc->mean_x += alpha * sc->mean_p;
         }
         sc->rr = rrn;
         if (kStoredLow<S> && rrn > sc->rr_max) sc->rr_max = rrn;
