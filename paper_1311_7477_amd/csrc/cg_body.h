@@ -211,9 +211,9 @@ struct StagedFaces {
     __device__ double* row(int wave) { return v + wave * kWave; }
 };
 
-// Whether the Laplacian stages canonical rows: from n = 3 on; below, a cell is
-// at most 32 contiguous bytes and lanes reading their own are as fast (n = 2,
-// 512^2: 11.2 us, staged 12.1).
+// Whether canonical rows may be staged: from n = 3 on; below, a cell is at most 32
+// contiguous bytes and lanes reading their own are as fast (Laplacian n = 2, 512^2:
+// 11.2 us, staged 12.1).
 constexpr bool staged_rows(int n) { return n >= 3; }
 
 // Waves of the Laplacian on a grid with cell tiles of cw waves: at n = 5 only
@@ -420,9 +420,9 @@ __device__ __forceinline__ double wsum_cell(const OpConst<double>& k, const doub
     return s * k.wq;
 }
 
-template <int N, class T>
+template <int N, class T, bool Staged>
 struct SrcCanon {                       // u = f (canonical layout)
-    static constexpr bool kStaged = staged_rows(N);
+    static constexpr bool kStaged = Staged;
     const T* f;
     __device__ void operator()(const CellRef& c, T (&u)[N * N]) const { ld_canon<N>(f, c, u); }
     __device__ void row(long o, int count, double* buf, int lane, T (&u)[N * N]) const {
@@ -496,18 +496,22 @@ struct SrcGuess {                       // x0 = ca pa + cb pb, canonical
 // through LDS against lanes loading and storing their own cells, n = 3,
 // 1153 x 701 36.9 -> 31.0 us; n = 4, 512^2 22.1 -> 16.0; n = 5, 2048^2 488 ->
 // 325 us (5.2 TB/s, a plain copy's rate).
+// Staged or not by the grid (laplace_staged).
 template <int N, int WV>
 using LaplaceLds = std::conditional_t<staged_rows(N), StagedFaces<N, WV>, YFaces<N, double, WV>>;
 
-template <int N, int WV, bool DIR = false, bool ISO = false>
+template <int N, int WV, bool Staged>
+using RowsLds = std::conditional_t<Staged, StagedFaces<N, WV>, PairFaces<N, double, WV>>;
+
+template <int N, int WV, bool DIR, bool ISO, bool Staged>
 __device__ __forceinline__ void laplace_body(
     int b, Geom g, int tilesX, int nblocks, const OpConst<double>& k,
     const double* __restrict__ u, double* __restrict__ out,
-    LaplaceLds<N, WV>& lds) {
+    RowsLds<N, WV, Staged>& lds) {
     const CellCtx c = make_cell_ctx<N, WV>(g, tilesX, nblocks, b);
-    SrcCanon<N, double> src{u};
+    SrcCanon<N, double, Staged> src{u};
     double v[N * N], lap[N * N];
-    if constexpr (staged_rows(N)) {
+    if constexpr (Staged) {
         src.row(c.row0, c.count, lds.row(c.wave), c.lane, v);
         lap_cell<N, WV, DIR, ISO>(c, k, src, v, lds, lap);
         __syncthreads();      // the face scalars are read: the buffers are free

@@ -9,12 +9,12 @@
 
 namespace dgk {
 
-template <int N, int WV, bool DIR, bool ISO>
+template <int N, int WV, bool DIR, bool ISO, bool STAGED>
 __global__ __launch_bounds__(64 * WV) void k_laplace(
     Geom g, int tilesX, int nblocks, OpConst<double> k,
     const double* __restrict__ u, double* __restrict__ out) {
-    __shared__ LaplaceLds<N, WV> lds;
-    laplace_body<N, WV, DIR, ISO>(blockIdx.x, g, tilesX, nblocks, k, u, out, lds);
+    __shared__ RowsLds<N, WV, STAGED> lds;
+    laplace_body<N, WV, DIR, ISO, STAGED>(blockIdx.x, g, tilesX, nblocks, k, u, out, lds);
 }
 
 template <int N, int WV, bool DIR, bool ISO>
@@ -77,33 +77,55 @@ bool iso_dir(const Geom& g, const OpConst<double>& k) {
     return g.bcx && g.bcy && k.ihx == k.ihy;
 }
 
+// Whether the Laplacian of a grid stages its rows of cells, against lanes reading
+// their own.  Staging moves whole runs of 64 cells, so it loses where a wave's row is
+// short, and where the halo rows are most of what a tile reads; with walls it also takes
+// the registers of a wave per SIMD.  us, lanes and staged:
+// periodic  n = 3, 1 x 40000 29.7 and 36.7; n = 4, 12 x 3333 8.7 and 10.0, 48 x 833
+//           equal, 512^2 22.1 and 16.0; n = 5, 32 x 1250 10.5 and 11.7, 16384 x 5 13.5 and
+//           15.1, 8 rows equal, 8^2 9.2 and 7.1
+// walls     n = 3, 333 x 257 7.2 and 8.3, 16384 x 12 13.3 and 11.0, 512^2 13.4 and 10.3; n
+//           = 4, walls all round, 100 x 400 10.4 and 12.2, 180^2 9.8 and 8.4, 1024^2 68.8 and
+//           57.2; two periodic sides, 128^2 8.9 and 9.4, 256^2 10.5 and 10.1, 1448^2 138 and
+//           145; n = 5, 32 x 1250 14.4 and 18.1, 128^2 18.6 and 12.1, two periodic sides,
+//           48^2 11.2 and 12.7, 128^2 12.9 and 12.2
+static bool laplace_staged(const Geom& g) {
+    if (!staged_rows(g.n)) return false;
+    const long cells = (long)g.nx * g.ny, lanes = 64L * ((g.nx + 63) / 64);
+    const bool all = g.bcx && g.bcy, mixed = !all && dirichlet(g);
+    if (g.n == 5 && !mixed && cells <= 4096) return true;
+    if (!dirichlet(g)) return g.nx >= 40 && (g.n < 5 || g.ny >= 8);
+    if (g.n == 5) return 4 * g.nx >= 3 * lanes && g.ny >= 8 && (all || cells >= 4096);
+    if (8 * g.nx < 7 * lanes) return false;
+    if (g.n == 3) return g.ny >= 8 && cells >= 150000;
+    if (g.ny < 32) return false;
+    return all ? g.nx >= 128 && cells >= 30000 : cells >= 60000 && cells < 1600000;
+}
+
 hipError_t launch_laplace(const Geom& g, const OpConst<double>& k,
                           const double* u, double* out, hipStream_t s) {
-    CellLaunch L(g, laplace_waves(g.n, g.cw));
+    const bool staged = laplace_staged(g);
+    const CellLaunch L(g, staged ? laplace_waves(g.n, g.cw) : cell_waves(g.n, g.cw));
+#define DG_LAP_W(W, DIR, ISO, STAGED)                                                             \
+    hipLaunchKernelGGL((k_laplace<NN, W, DIR, ISO, STAGED>), dim3(L.nblocks), dim3(64 * (W)), 0,  \
+                       s, g, L.tilesX, L.nblocks, k, u, out)
+#define DG_LAP(W, DIR, ISO)                                                     \
+    if (staged) DG_LAP_W(laplace_waves(NN, W), DIR, ISO, staged_rows(NN));      \
+    else DG_LAP_W(cell_waves(NN, W), DIR, ISO, false)
     if (dirichlet(g)) {
         if (g.cw != kDirichletCellWaves) return hipErrorInvalidValue;
         if (iso_dir(g, k)) {
-            DG_DISPATCH_N(g.n, hipLaunchKernelGGL((k_laplace<NN, laplace_waves(NN, kDirichletCellWaves), true, true>),
-                                                  dim3(L.nblocks), dim3(64 * laplace_waves(NN, kDirichletCellWaves)),
-                                                  0, s, g, L.tilesX, L.nblocks, k, u, out));
+            DG_DISPATCH_N(g.n, DG_LAP(kDirichletCellWaves, true, true));
         } else {
-            DG_DISPATCH_N(g.n, hipLaunchKernelGGL((k_laplace<NN, laplace_waves(NN, kDirichletCellWaves), true, false>),
-                                                  dim3(L.nblocks), dim3(64 * laplace_waves(NN, kDirichletCellWaves)),
-                                                  0, s, g, L.tilesX, L.nblocks, k, u, out));
+            DG_DISPATCH_N(g.n, DG_LAP(kDirichletCellWaves, true, false));
         }
-        return hipGetLastError();
-    }
-    if (iso(g, k)) {
-        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_laplace<NN, laplace_waves(NN, WW), false, true>),
-                                                     dim3(L.nblocks),
-                                              dim3(64 * laplace_waves(NN, WW)), 0, s, g, L.tilesX,
-                                              L.nblocks, k, u, out));
+    } else if (iso(g, k)) {
+        DG_DISPATCH_NW(g.n, g.cw, DG_LAP(WW, false, true));
     } else {
-        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_laplace<NN, laplace_waves(NN, WW), false, false>),
-                                                     dim3(L.nblocks),
-                                              dim3(64 * laplace_waves(NN, WW)), 0, s, g, L.tilesX,
-                                              L.nblocks, k, u, out));
+        DG_DISPATCH_NW(g.n, g.cw, DG_LAP(WW, false, false));
     }
+#undef DG_LAP
+#undef DG_LAP_W
     return hipGetLastError();
 }
 
