@@ -389,6 +389,7 @@ int pcg_queue(const dg_grid* g, const double* omega, const double* pa, double ca
                                   o.max_iter, d, s);
     if (e != hipSuccess) return hip_fail(e, "cg mean launch");
     InitImage img;
+    img.on = 1;
     const int layout = fd_layout(ws->fd);
     img.dense = layout == kFdDense;
     if (layout != kFdFolded) {

@@ -39,7 +39,7 @@ __global__ __launch_bounds__(kPwThreads) void kb_cg_mean(const BatchInst* __rest
 
 template <int N, int WV>
 __global__ __launch_bounds__(64 * WV, (N <= 4 ? 4 : 1)) void kb_cg_init(const BatchInst* __restrict__ inst, ItemList list) {
-    __shared__ YFaces<N, double, WV> lds;
+    __shared__ PairFaces<N, double, WV> lds;
     DG_FOR_ITEMS(list) {
         cg_init_body<N, WV>(item_.b, B.g, B.cell_tilesX, B.cell_nblocks, B.k, B.w_in,
                         B.pa, B.pb, B.ca, B.cb, 1.0 / B.area, B.x, B.r, B.sc,

@@ -561,19 +561,19 @@ __device__ __forceinline__ void put_image(const Geom& g, const OpConst<double>& 
 
 // CG setup (stencil part): x0 = guess (to L64; its mean is left in, see
 // cg_mean_body);
-// r0 = (omega - mean(omega)) + Lap_h x0 (to L64); partials <r0,r0>_W, <b,b>_W,
-// <x0,1>_W (inv_area: 1 / area, 0 with a Dirichlet axis).  A preconditioned solve
-// has r0 put into the preconditioner's work field as well where its layout takes
-// whole cells (img), which spares a pass that reads r0 again (setup and that pass
+// r0 = (omega - mean(omega)) + Lap_h x0 (to L64); partials <r0,r0>_W, <b,b>_W.
+// PRE, a preconditioned solve, also sums <x0,1>_W (inv_area: 1 / area, 0 with a
+// Dirichlet axis) and puts r0 into the preconditioner's work field where its layout
+// takes whole cells, which spares a pass that reads r0 again (setup and that pass
 // n = 4, 512^2 38 + 12 -> 42 us; n = 5, 1024^2, FP32 205 + 55 -> 217 us).
-template <int N, int WV, bool DIR = false, bool ISO = false>
+template <int N, int WV, bool DIR = false, bool ISO = false, bool PRE = false>
 __device__ __forceinline__ void cg_init_body(
     int b, Geom g, int tilesX, int nblocks, const OpConst<double>& k,
     const double* __restrict__ omega, const double* __restrict__ pa,
     const double* __restrict__ pb, double ca, double cb, double inv_area,
     double* __restrict__ x, double* __restrict__ r, CgScalars* sc,
     unsigned* counter, double* partials,
-    YFaces<N, double, WV>& lds, const InitImage& img = InitImage()) {
+    PairFaces<N, double, WV>& lds, const InitImage& img = InitImage()) {
     const CellCtx c = make_cell_ctx<N, WV>(g, tilesX, nblocks, b);
     SrcGuess<N> src{pa, pb, ca, cb};
     const double mo = sc->mean_omega;
@@ -581,7 +581,10 @@ __device__ __forceinline__ void cg_init_body(
     if (c.active) src(c.self, x0);
     else zero_cell<N>(x0);
     lap_cell<N, WV, DIR, ISO>(c, k, src, x0, lds, lap);
-    double part[3] = {0.0, 0.0, 0.0};
+    constexpr int NV = PRE ? 3 : 2;
+    double part[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) part[v] = 0.0;
     if (c.active) {
         double bv[N * N];
         ld_canon<N>(omega, c.self, bv);
@@ -594,17 +597,19 @@ __device__ __forceinline__ void cg_init_body(
         st_l64<N>(r, c.self, lap);
         part[0] = wdot_cell<N>(k, lap, lap);
         part[1] = wdot_cell<N>(k, bv, bv);
-        part[2] = wsum_cell<N>(k, x0);
-        const long cell = c.self.canon / (N * N);
-        if (img.d && !img.dense) put_image<N, false>(g, k, cell, lap, img.d);
-        else if (img.f && !img.dense) put_image<N, false>(g, k, cell, lap, img.f);
-        else if (DIR && img.d) put_image<N, true>(g, k, cell, lap, img.d);
-        else if (DIR && img.f) put_image<N, true>(g, k, cell, lap, img.f);
+        if constexpr (PRE) {
+            part[2] = wsum_cell<N>(k, x0);
+            const long cell = c.self.canon / (N * N);
+            if (img.d && !img.dense) put_image<N, false>(g, k, cell, lap, img.d);
+            else if (img.f && !img.dense) put_image<N, false>(g, k, cell, lap, img.f);
+            else if (DIR && img.d) put_image<N, true>(g, k, cell, lap, img.d);
+            else if (DIR && img.f) put_image<N, true>(g, k, cell, lap, img.f);
+        }
     }
-    double tot[3];
-    if (reduce_last<3, 64 * WV>(part, partials, counter, nblocks, b, tot) &&
+    double tot[NV];
+    if (reduce_last<NV, 64 * WV>(part, partials, counter, nblocks, b, tot) &&
         threadIdx.x == 0) {
-        sc->mean_x = tot[2] * inv_area;
+        if constexpr (PRE) sc->mean_x = tot[2] * inv_area;
         sc->rr = tot[0];
         sc->rz = tot[0];
         sc->bb = tot[1];

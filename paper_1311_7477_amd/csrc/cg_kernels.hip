@@ -17,16 +17,16 @@ __global__ __launch_bounds__(64 * WV) void k_laplace(
     laplace_body<N, WV, DIR, ISO, STAGED>(blockIdx.x, g, tilesX, nblocks, k, u, out, lds);
 }
 
-template <int N, int WV, bool DIR, bool ISO>
+template <int N, int WV, bool DIR, bool ISO, bool PRE>
 __global__ __launch_bounds__(64 * WV) void k_cg_init(
     Geom g, int tilesX, int nblocks, OpConst<double> k,
     const double* __restrict__ omega, const double* __restrict__ pa,
     const double* __restrict__ pb, double ca, double cb, double inv_area,
     double* __restrict__ x, double* __restrict__ r, CgScalars* sc,
     unsigned* counter, double* partials, InitImage img) {
-    __shared__ YFaces<N, double, WV> lds;
-    cg_init_body<N, WV, DIR, ISO>(blockIdx.x, g, tilesX, nblocks, k, omega, pa, pb, ca, cb, inv_area, x,
-                             r, sc, counter, partials, lds, img);
+    __shared__ PairFaces<N, double, WV> lds;
+    cg_init_body<N, WV, DIR, ISO, PRE>(blockIdx.x, g, tilesX, nblocks, k, omega, pa, pb, ca, cb,
+                                       inv_area, x, r, sc, counter, partials, lds, img);
 }
 
 // At n = 4 the periodic direction and residual kernels are held to 128
@@ -135,36 +135,27 @@ hipError_t launch_cg_init(const Geom& g, const OpConst<double>& k,
                           double* r, const DevScratch& d, hipStream_t s, const InitImage& img) {
     CellLaunch L(g);
     const double inv_area = dirichlet(g) ? 0.0 : 1.0 / area;
+#define DG_INIT(W, DIR, ISO, PRE)                                                                \
+    hipLaunchKernelGGL((k_cg_init<NN, W, DIR, ISO, PRE>), dim3(L.nblocks), dim3(64 * (W)), 0, s, \
+                       g, L.tilesX, L.nblocks, k, omega, pa, pb, ca, cb, inv_area, x, r, d.sc,   \
+                       d.counters + kCntInit * kCntStride, d.partials, img)
+#define DG_INIT_PRE(W, DIR, ISO)             \
+    if (img.on) DG_INIT(W, DIR, ISO, true);  \
+    else DG_INIT(W, DIR, ISO, false)
     if (dirichlet(g)) {
         if (g.cw != kDirichletCellWaves) return hipErrorInvalidValue;
         if (iso_dir(g, k)) {
-            DG_DISPATCH_N(g.n, hipLaunchKernelGGL((k_cg_init<NN, kDirichletCellWaves, true, true>),
-                                                  dim3(L.nblocks), dim3(64 * kDirichletCellWaves),
-                                                  0, s, g, L.tilesX, L.nblocks, k, omega, pa, pb,
-                                                  ca, cb, inv_area, x, r, d.sc, d.counters + kCntInit * kCntStride,
-                                                  d.partials, img));
+            DG_DISPATCH_N(g.n, DG_INIT_PRE(kDirichletCellWaves, true, true));
         } else {
-            DG_DISPATCH_N(g.n, hipLaunchKernelGGL((k_cg_init<NN, kDirichletCellWaves, true, false>),
-                                                  dim3(L.nblocks), dim3(64 * kDirichletCellWaves),
-                                                  0, s, g, L.tilesX, L.nblocks, k, omega, pa, pb,
-                                                  ca, cb, inv_area, x, r, d.sc, d.counters + kCntInit * kCntStride,
-                                                  d.partials, img));
+            DG_DISPATCH_N(g.n, DG_INIT_PRE(kDirichletCellWaves, true, false));
         }
-        return hipGetLastError();
-    }
-    if (iso(g, k)) {
-        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_cg_init<NN, cell_waves(NN, WW), false, true>),
-                                                     dim3(L.nblocks),
-                                              dim3(64 * cell_waves(NN, WW)), 0, s, g, L.tilesX,
-                                              L.nblocks, k, omega, pa, pb, ca, cb, inv_area, x, r,
-                                              d.sc, d.counters + kCntInit * kCntStride, d.partials, img));
+    } else if (iso(g, k)) {
+        DG_DISPATCH_NW(g.n, g.cw, DG_INIT_PRE(cell_waves(NN, WW), false, true));
     } else {
-        DG_DISPATCH_NW(g.n, g.cw, hipLaunchKernelGGL((k_cg_init<NN, cell_waves(NN, WW), false, false>),
-                                                     dim3(L.nblocks),
-                                              dim3(64 * cell_waves(NN, WW)), 0, s, g, L.tilesX,
-                                              L.nblocks, k, omega, pa, pb, ca, cb, inv_area, x, r,
-                                              d.sc, d.counters + kCntInit * kCntStride, d.partials, img));
+        DG_DISPATCH_NW(g.n, g.cw, DG_INIT_PRE(cell_waves(NN, WW), false, false));
     }
+#undef DG_INIT_PRE
+#undef DG_INIT
     return hipGetLastError();
 }
 

@@ -117,9 +117,11 @@ struct RhsArgs {
     int only_r;
 };
 
-// The preconditioner's work field, in FP64 or FP32, for the CG setup to fill
-// (neither: it does not); dense: as the image the eigenbasis path takes.
+// What the setup of a preconditioned solve (on) does beyond a plain one's: it sums the
+// guess's mean, and fills the preconditioner's work field, in FP64 or FP32 (neither:
+// it does not); dense: as the image the eigenbasis path takes.
 struct InitImage {
+    int on = 0;
     double* d = nullptr;
     float* f = nullptr;
     int dense = 0;
