@@ -33,29 +33,15 @@ __device__ __forceinline__ void cg_mean_body(int b, int nb, long rows, const OpC
     (void)pa;
     (void)pb;
     double part[2] = {0.0, 0.0};
-    // four rows in flight per thread
-    constexpr int U = 4;
-    const long step = (long)nb * kPwThreads;
-    for (long row0 = b * (long)kPwThreads + threadIdx.x; row0 < rows; row0 += U * step) {
-        double w[U][N];
+    for (long row = b * (long)kPwThreads + threadIdx.x; row < rows;
+         row += (long)nb * kPwThreads) {
+        const int j = (int)(row % N);
+        double w[N], w2[N];
+        load_vec(omega, row * N, w);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (row0 + u * step < rows) {
-                load_vec(omega, (row0 + u * step) * N, w[u]);
-            } else {
-#pragma unroll
-                for (int i = 0; i < N; ++i) w[u][i] = 0.0;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int j = (int)((row0 + u * step) % N);
-            double w2[N];
-#pragma unroll
-            for (int i = 0; i < N; ++i) w2[i] = w[u][i] * w[u][i];
-            part[0] += wrow<N>(k, j, w[u]);
-            part[1] += wrow<N>(k, j, w2);
-        }
+        for (int i = 0; i < N; ++i) w2[i] = w[i] * w[i];
+        part[0] += wrow<N>(k, j, w);
+        part[1] += wrow<N>(k, j, w2);
     }
     double tot[2];
     if (reduce_last<2, kPwThreads>(part, partials, counter, nb, b, tot) &&
@@ -184,34 +170,20 @@ __device__ __forceinline__ void invariants_body(int b, int nb, long rows, const 
     const double* __restrict__ psi, double* out3, unsigned* counter,
     double* partials) {
     double part[3] = {0.0, 0.0, 0.0};
-    // two rows of each field in flight per thread
-    constexpr int U = 2;
-    const long step = (long)nb * kPwThreads;
-    for (long row0 = b * (long)kPwThreads + threadIdx.x; row0 < rows; row0 += U * step) {
-        double w[U][N], p[U][N];
+    for (long row = b * (long)kPwThreads + threadIdx.x; row < rows;
+         row += (long)nb * kPwThreads) {
+        const int j = (int)(row % N);
+        double w[N], p[N], pw[N], ww[N];
+        load_vec(omega, row * N, w);
+        load_vec(psi, row * N, p);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (row0 + u * step < rows) {
-                load_vec(omega, (row0 + u * step) * N, w[u]);
-                load_vec(psi, (row0 + u * step) * N, p[u]);
-            } else {
-#pragma unroll
-                for (int i = 0; i < N; ++i) w[u][i] = p[u][i] = 0.0;
-            }
+        for (int i = 0; i < N; ++i) {
+            pw[i] = p[i] * w[i];
+            ww[i] = w[i] * w[i];
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int j = (int)((row0 + u * step) % N);
-            double pw[N], ww[N];
-#pragma unroll
-            for (int i = 0; i < N; ++i) {
-                pw[i] = p[u][i] * w[u][i];
-                ww[i] = w[u][i] * w[u][i];
-            }
-            part[0] += wrow<N>(k, j, w[u]);
-            part[1] += wrow<N>(k, j, pw);
-            part[2] += wrow<N>(k, j, ww);
-        }
+        part[0] += wrow<N>(k, j, w);
+        part[1] += wrow<N>(k, j, pw);
+        part[2] += wrow<N>(k, j, ww);
     }
     double tot[3];
     if (reduce_last<3, kPwThreads>(part, partials, counter, nb, b, tot) &&
