@@ -125,14 +125,32 @@ bool valid_mode(int mode) {
     return prec == DG_PREC_FP64 || prec == DG_PREC_MIXED;
 }
 
+// The two RK stage fields.  The plain CG of a periodic grid needs one more L64 vector,
+// its second residual (second_residual): the vector of a preconditioned or of an
+// FP32-stored solve where the workspace has those, else the stage field that does not
+// hold its input, with room beside it for what an L64 vector is longer, shared by the
+// two: [s1 | ... | s2], the residual from the start or from the end of s1.
+struct StageFields {
+    size_t s2, total;      // offset of s2, and doubles in all
+    StageFields(const dg_grid* g, int mode) {
+        const size_t F = g->elems, L = l64_elems(g->geom);
+        const bool shared = !g->geom.bcx && !g->geom.bcy && !(mode & DG_WS_FD) &&
+                            prec_of(mode) != DG_PREC_MIXED;
+        s2 = even(F) + (shared ? even(L - F) : 0);
+        total = s2 + F;
+    }
+    static size_t even(size_t n) { return (n + 1) & ~(size_t)1; }
+};
+
 size_t ws_bytes(const dg_grid* g, int mode) {
     const size_t F = g->elems * sizeof(double);
     const size_t L = l64_elems(g->geom);
     int blocks = stencil_blocks(g->geom);
     if (blocks < pointwise_block_cap()) blocks = pointwise_block_cap();
-    size_t b = 6 * L * sizeof(double);                  // x, r, p0, p1; s1, s2
+    size_t b = 4 * L * sizeof(double);                  // x, r, p0, p1
+    b += StageFields(g, mode).total * sizeof(double);   // s1, s2
     b += (size_t)blocks * 4 * sizeof(double);           // partials
-    b += step_part_bytes(g->geom);
+    if (!g->geom.bcx && !g->geom.bcy) b += step_part_bytes(g->geom);
     b += 2 * sizeof(CgScalars) + kCntBytes + 4 * sizeof(double);
     if (prec_of(mode) == DG_PREC_MIXED) b += 3 * L * sizeof(float);
     if (mode & DG_WS_FD)
@@ -219,8 +237,7 @@ int cg_loop(int total, int chunk, const CgScalars* sc, dg_workspace* ws, hipStre
 // to an even count (after which sc[0] is the newest), or none for max_iter = 0.
 int cg_steps(const dg_grid* g, const double* omega, const dg_cg_opts& o, dg_workspace* ws,
              hipStream_t s, CgScalars* fin) {
-    // the second residual takes the RK field that does not hold the input
-    StepBuffers v{ws->x, ws->r, omega == ws->s1 ? ws->s2 : ws->s1, ws->p0, ws->p1,
+    StepBuffers v{ws->x, ws->r, second_residual(ws, omega), ws->p0, ws->p1,
                   {ws->d.sc, ws->d.sc + 1}, g->scale, ws->step_part, ws->step_max_blocks};
     const int most = o.max_iter < (1 << 30) ? o.max_iter : (1 << 30);
     const int total = most > 0 ? (most + 3) & ~1 : 0;
@@ -539,6 +556,12 @@ int periodic_only(const char* what) {
                 "or preconditioned, the mixed-precision PCG and time stepping)", what);
 }
 
+double* second_residual(const dg_workspace* ws, const double* input) {
+    if (ws->z) return ws->z;
+    if (ws->r32) return reinterpret_cast<double*>(ws->r32);      // r32 and q0
+    return input == ws->s1 ? ws->s1 + StageFields::even(ws->elems) : ws->s1;
+}
+
 int solve_poisson(const dg_grid* g, const double* omega, double* x, const double* pa,
                   double ca, const double* pb, double cb, const dg_cg_opts* opts,
                   dg_cg_stats* st, dg_workspace* ws, hipStream_t s) {
@@ -615,8 +638,7 @@ void dg_workspace_destroy(dg_workspace* ws) {
     int cur = -1;
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(ws->device);
-    void* bufs[] = {ws->x, ws->r, ws->p0, ws->p1, ws->s1, ws->s2, ws->r32,
-                    ws->q0, ws->q1, ws->z, ws->wbak, ws->sc3, ws->d.sc, ws->d.counters,
+    void* bufs[] = {ws->x, ws->r, ws->p0, ws->p1, ws->s1, ws->r32, ws->z, ws->wbak, ws->sc3, ws->d.sc, ws->d.counters,
                     ws->d.partials, ws->d.out3, ws->step_part};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
@@ -654,21 +676,25 @@ int dg_workspace_create(const dg_grid* g, int mode, dg_workspace** out) {
         return hipMalloc(p, b) == hipSuccess;
     };
     const size_t L = l64_elems(g->geom);
+    const StageFields stage(g, mode);
     bool ok = alloc((void**)&ws->x, L * sizeof(double)) &&
               alloc((void**)&ws->r, L * sizeof(double)) &&
               alloc((void**)&ws->p0, L * sizeof(double)) &&
               alloc((void**)&ws->p1, L * sizeof(double)) &&
-              alloc((void**)&ws->s1, L * sizeof(double)) &&
-              alloc((void**)&ws->s2, L * sizeof(double)) &&
+              alloc((void**)&ws->s1, stage.total * sizeof(double)) &&
               alloc((void**)&ws->d.sc, 2 * sizeof(CgScalars)) &&
-              alloc((void**)&ws->step_part, step_part_bytes(g->geom)) &&
               alloc((void**)&ws->d.counters, kCntBytes) &&
               alloc((void**)&ws->d.partials, (size_t)blocks * 4 * sizeof(double)) &&
               alloc((void**)&ws->d.out3, 4 * sizeof(double));
+    if (ok) ws->s2 = ws->s1 + stage.s2;
+    if (ok && !g->geom.bcx && !g->geom.bcy)
+        ok = alloc((void**)&ws->step_part, step_part_bytes(g->geom));
     if (ok && prec_of(mode) == DG_PREC_MIXED) {
-        const size_t f32 = L * sizeof(float);
-        ok = alloc((void**)&ws->r32, f32) && alloc((void**)&ws->q0, f32) &&
-             alloc((void**)&ws->q1, f32);
+        ok = alloc((void**)&ws->r32, 3 * L * sizeof(float));
+        if (ok) {
+            ws->q0 = ws->r32 + L;
+            ws->q1 = ws->r32 + 2 * L;
+        }
     }
     if (ok && (mode & DG_WS_FD))
         ok = alloc((void**)&ws->z, L * sizeof(double)) && alloc((void**)&ws->wbak, F) &&

@@ -26,10 +26,9 @@ struct dg_workspace {
     int n, nx, ny, mode, device;
     size_t elems;
     double *x, *r, *p0, *p1;   // CG vectors, lane-interleaved layout
-    double *s1, *s2;           // RK stage fields, canonical layout; the plain CG keeps its
-                               // second residual in the one that does not hold its input
-                               // (both sized for an L64 vector)
-    float *r32, *q0, *q1;      // mixed precision: FP32 residual and directions
+    double *s1, *s2;           // RK stage fields, canonical layout, in one allocation (s1)
+    float *r32, *q0, *q1;      // mixed precision: FP32 residual and directions, in one
+                               // allocation (r32)
     double* z;                 // preconditioned residual (DG_WS_FD workspaces)
     double* wbak;              // DG_WS_FD: omega at the start of a queued RK step
     CgScalars* sc3;            // DG_WS_FD: device scalars of the three queued stage solves
@@ -83,6 +82,9 @@ int form_coeffs(int form, double* c0, double* c1, double* c2, double* scale);
 int solve_poisson(const dg_grid* g, const double* omega, double* x, const double* pa,
                   double ca, const double* pb, double cb, const dg_cg_opts* opts,
                   dg_cg_stats* st, dg_workspace* ws, hipStream_t s);
+// Where the plain CG of a periodic grid keeps its second residual (an L64 vector)
+// while it solves for `input`: in memory that such a solve does not need otherwise.
+double* second_residual(const dg_workspace* ws, const double* input);
 // Fast-diagonalisation preconditioner resources (fd_apply.cpp): device bytes,
 // creation / destruction, and z = M r on the image buffer img0 in place.
 size_t fd_bytes(const dg_grid* g);

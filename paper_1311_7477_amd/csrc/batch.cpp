@@ -549,7 +549,7 @@ int dg_batch_rk_step(dg_batch* b, const dg_cg_opts* opts, int* iters_out,
             double* win[3] = {sl.omega, sl.ws->s1, sl.ws->s2};
             double* wout[3] = {sl.ws->s1, sl.ws->s2, sl.omega};
             r.w_in = win[k];
-            r.r1 = win[k] == sl.ws->s1 ? sl.ws->s2 : sl.ws->s1;
+            r.r1 = second_residual(sl.ws, win[k]);
             r.w_out = wout[k];
             r.w_n = k ? sl.omega : nullptr;
             r.ra = RhsArgs{1.0, 1.0, 1.0, 1.0 / 3.0, sl.D, sl.dt, ra_a[k], ra_b[k], 0};

@@ -38,7 +38,7 @@ struct BatchInst {
     double* psi;           // solve output (canonical)
     RhsArgs ra;
     // workspace
-    double *x, *r, *r1, *p0, *p1;   // r1: stage part (the free RK field)
+    double *x, *r, *r1, *p0, *p1;   // r1: stage part (second_residual)
     CgScalars* sc;
     CgScalars* sc1;          // scalars of odd CG launches
     double* step_part;       // block sums of the CG launches, two parities
