@@ -178,8 +178,8 @@ int harvest_profile(dg_workspace* ws, int slot, int device_iter) {
     if (device_iter >= ws->pev_iter[slot]) {
         float a = 0.f;
         HIP_TRY(hipEventElapsedTime(&a, ws->pev[slot][0], ws->pev[slot][1]));
-        ws->prof_ms[0] += a;
-        ws->prof_n[0] += 1;
+        ws->prof_ms += a;
+        ws->prof_n += 1;
     }
     ws->pev_iter[slot] = -1;
     return DG_OK;
@@ -753,11 +753,10 @@ int dg_profile_enable(dg_workspace* ws, int on) {
 
 int dg_profile_read(dg_workspace* ws, double* out4) {
     if (!ws || !out4) return fail(DG_E_INVAL, "NULL argument");
-    out4[0] = ws->prof_ms[0];
-    out4[1] = ws->prof_n[0];
-    out4[2] = ws->prof_ms[1];
-    out4[3] = ws->prof_n[1];
-    ws->prof_ms[0] = ws->prof_ms[1] = ws->prof_n[0] = ws->prof_n[1] = 0.0;
+    out4[0] = ws->prof_ms;
+    out4[1] = ws->prof_n;
+    out4[2] = out4[3] = 0.0;
+    ws->prof_ms = ws->prof_n = 0.0;
     return DG_OK;
 }
 

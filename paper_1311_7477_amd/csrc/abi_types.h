@@ -42,10 +42,10 @@ struct dg_workspace {
     size_t bytes;
     // live kernel timing (measurement support)
     int prof_on;
-    hipEvent_t pev[2][4];
-    int pev_iter[2];           // iteration index sampled in that poll slot (-1: none)
-    double prof_ms[2];         // summed ms of sampled direction / residual launches
-    double prof_n[2];
+    hipEvent_t pev[2][2];
+    int pev_iter[2];           // launch sampled in that poll slot (-1: none)
+    double prof_ms;            // summed ms and number of the sampled launches
+    double prof_n;
 };
 
 struct dg_state {
