@@ -427,22 +427,38 @@ __global__ __launch_bounds__(64, N >= 4 ? 1 : 2) void k_rhs_strip(
 
 }  // namespace
 
-// Waves resident at a time, by order (registers), and the rows of cells each
-// gets, all of them in one go, for the grid to take strips.  A run begins with
-// two rows that only give traces, so short runs lose: bracket, strips against
-// rows per lane, n = 4, 512^2 (4.5 rows) 33.7 and 28.4 us, 1024^2 (17) 102 and
-// 115; n = 3, 512^2 (2.2 rows) 19.1 and 18.5, 700^2 (4.1) 28.2 and 30.5; n = 2,
-// 700^2 (2) 15.2 and 13.3, 1024^2 (4.3) 25.4 and 26.2.  And no strips where more
-// than a quarter of the lanes would be idle.
+// Waves resident at a time, by order (registers); all strips run in one go.
 constexpr int kStripWaves[kMaxN + 1] = {0, 6144, 4096, 2048, 1024, 1024};
 
 int strip_count(const Geom& g) { return (g.nx + 61) / 62; }
 
+// Grids that take strips.  A run begins with two rows that only give traces, so
+// short runs lose, and so do strips with idle lanes.  Bracket, rows per lane ->
+// strips, us (rows of cells per wave, part of the lanes used):
+//   n = 1: 1000^2 (2.8) 9.0 -> 9.3; 1200^2 (3.9) 11.2 -> 9.2; 94 x 18000 (5.9,
+//     0.76) 15.1 -> 11.3
+//   n = 2: 1024^2 (4.3) 22.4 -> 25.1; 1100^2 (4.8) 27.2 -> 25.9; 1300^2 (6.7) 38.1
+//     -> 34.1; 94 x 12492 (6.1, 0.76) 33.8 -> 28.8; 140 x 8328 (6.1, 0.75) 27.7 -> 29.1
+//   n = 3: 512^2 (2.3) 18.2 -> 18.6; 700^2 (4.1) 28.6 -> 26.6; 94 x 6246 (6.1, 0.76)
+//     39.4 -> 35.9
+//   n = 4: 512^2 (4.5) 27.9 -> 32.7; 700^2 (8.2) 47.2 -> 51.3; 800^2 (10.2) 67.3 ->
+//     64.6; 1024^2 (17) 110 -> 101; 140 x 3000 (8.8, 0.75) 41.0 -> 49.7; 94 x 20480
+//     (40, 0.76) 204 -> 214; 118 x 10240 (20, 0.95) 134 -> 122
+//   n = 5: 512^2 (4.5) 52.4 -> 53.4; 600^2 (5.9) 68.0 -> 63.2; 1024^2 (17) 206 ->
+//     183; 94 x 5120 (10, 0.76) 101 -> 103; 94 x 10240 (20, 0.76) 195 -> 185
+// From n = 4 on, where both kernels are bound by arithmetic, the line is one of
+// cost: a wave's rows and the two before them against 5/4 (n = 4) or 3/2 (n = 5)
+// of the rows that its cells would fill.
 bool rhs_strips(const Geom& g) {
     if (g.bcx || g.bcy || (long)g.nx * g.n * g.n >= 1L << 28) return false;
-    const long strips = strip_count(g), rows = g.n >= 4 ? 6 : 4;
-    return strips <= kStripWaves[g.n] && 4L * g.nx >= 3 * 62 * strips &&
-           strips * g.ny >= rows * kStripWaves[g.n];
+    const long strips = strip_count(g), waves = kStripWaves[g.n];
+    const long rows = strips * g.ny;
+    if (strips > waves) return false;
+    if (g.n >= 4) {
+        const long cost = 62 * (rows + 2 * waves), cells = (long)g.nx * g.ny;
+        return g.n == 4 ? 4 * cost < 5 * cells : 2 * cost < 3 * cells;
+    }
+    return 4L * g.nx >= 3 * 62 * strips && rows >= (g.n == 2 ? 5 : 4) * waves;
 }
 
 hipError_t launch_rhs_strip(const Geom& g, const OpConst<double>& k, const double* f,
