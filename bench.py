@@ -9,7 +9,8 @@ bracket/viscous/stage kernel).  value = Nx * Ny * RHS / second.
 
 Also reported: p50/p99 of the per-RHS device time (HIP events), CG
 iterations per RHS, the roofline figure of the dominant kernel (the CG
-direction-update kernel, timed live with HIP events on the solve stream),
+iteration kernel, timed live with HIP events on the solve stream, with its
+counted HBM bytes where they belong to the sources and the size at hand),
 and the FP64 oracle timed on the host on a bounded sample.
 """
 import argparse
@@ -28,13 +29,14 @@ if ROOT not in sys.path:
 METRIC = ("DG cell-updates/s per RHS (bracket+CG) at n=4, 512², 1 GPU; "
           "p50/p99 latency")
 HBM_PEAK_GBS = 8000.0
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "cg_dir_traffic_n4_512.json")
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "cg_step_traffic_n4_512.json")
 KERNEL_SRCS = [os.path.join(ROOT, "paper_1311_7477_amd", "csrc", f)
-               for f in ("cg_kernels.hip", "cg_body.h", "dg_device.h")]
+               for f in ("cg_step_kernels.hip", "cg_step_body.h", "cg_body.h",
+                         "dg_device.h", "dg_stage.h", "dg_internal.h")]
 
 
 def kernel_source_hash():
-    """sha256 (first 16 hex digits) of the sources the CG kernels are
+    """sha256 (first 16 hex digits) of the sources the CG iteration kernel is
     compiled from, concatenated."""
     h = hashlib.sha256()
     for f in KERNEL_SRCS:
@@ -44,9 +46,11 @@ def kernel_source_hash():
 
 
 def measured_traffic(F_bytes, cw):
-    """HBM bytes per launch of the direction kernel with cell tiles of cw
-    waves, from committed rocprofv3 FETCH_SIZE/WRITE_SIZE counters, or None
-    when they are missing or were taken on a different kernel source."""
+    """HBM bytes per launch of the CG iteration kernel on fields of F_bytes
+    (mean of the launches with and without the x update; its tiles do not
+    depend on the cell tile cw), from committed rocprofv3 FETCH_SIZE /
+    WRITE_SIZE counters, or None when they are missing, of another size, or
+    were taken on a different kernel source."""
     try:
         with open(TRAFFIC_FILE) as fh:
             t = json.load(fh)
@@ -54,7 +58,9 @@ def measured_traffic(F_bytes, cw):
         return None
     if t.get("kernel_source_sha256_16") != kernel_source_hash():
         return None
-    return t.get("bytes_per_launch_by_cw", {}).get(str(cw))
+    if t.get("field_bytes", F_bytes) != F_bytes:
+        return None
+    return t.get("bytes_per_launch")
 
 
 def cpu_baseline(n, N, omega0, psi0, D, dt, iters_per_rhs):
@@ -1038,7 +1044,7 @@ def main():
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
-            "traffic": None,
+            "traffic": measured_traffic(F, tiles[0]),
             "avg_launch_ms": ms_iter,
             "samples": n_iter,
             "algorithmic_bytes_per_launch": alg_bytes,

@@ -18,18 +18,19 @@
 // Per launch: read r, p; write r, p (4 fields); every other one also p_{k-2}
 // and x (7 fields) -- 5.5 on average against 7.5 of the two-launch form.
 // Microseconds per iteration, two launches -> this kernel: n = 3, 128^2
-// 16.5 -> 6.6; n = 4, 512^2 49.9 -> 39.0 (4.7 TB/s of the 5.5 fields); n = 5,
-// 1024^2 355 -> 288.  Small grids are bound by the chain of one launch (asking
+// 16.5 -> 6.6; n = 4, 512^2 49.5 -> 38.1 (4.8 TB/s of the 5.5 fields; counted,
+// 6.1 are moved: 4.1 without x, 8.0 with it, most likely as the halo rows of r and p
+// then no longer stay in the L2); n = 5, 1024^2 355 -> 288.  Small grids are bound by the chain of one launch (asking
 // for the cells and the previous sums at once, one barrier per operator, no
 // ticket), large ones by memory; in between a wave's loads, two operators and
 // stores follow one another with too few waves to overlap them wholly.
 //
 // r_k and p_k are needed one cell beyond the cells whose A p_k is summed, so a
 // tile is 64 x WV cells of which the inner 60 x (WV - 2) are summed and
-// stored (all 64 lanes on rows of 61 to 64 cells, step_rim); the rest is formed again by the neighbouring tiles (the two outer
-// lanes on each side have no valid neighbour and only feed the next ones; the
-// face scalars beyond the first and last cell row are taken from a row loaded
-// for them).  r and p are double-buffered.  Leaving face scalars for the
+// stored (all 64 lanes on rows of 61 to 64 cells, step_rim); the rest is formed
+// again by the neighbouring tiles (the two outer lanes on each side have no valid
+// neighbour and only feed the next ones; the face scalars beyond the first and last
+// cell row are taken from a row loaded for them).  r and p are double-buffered.  Leaving face scalars for the
 // neighbouring tiles in memory instead, so that no cell is formed twice, was
 // measured: what a rim wave has to read and do made every wave of its tile wait
 // (58 against 43 us per iteration at n = 4, 512^2; 9.9 against 7.0 us at n = 3,
