@@ -74,8 +74,8 @@ constexpr int kFdGemmMaxCells = 32;
 
 // The library's own product kernel (fd_gemm.hip) up to these operations per
 // transform, rocBLAS beyond.  Whole applications, own / rocBLAS, us: folded
-// pairs of halves, n = 3, 127 x 127 (1.8e7) 36 / 66, n = 4, 255 x 187 (1.7e8)
-// 81 / 107, 255 x 255 (2.7e8) 101 / 130, 401 x 401 (1.0e9) 264 / 233; single
+// pairs of halves, n = 3, 127 x 127 (1.8e7) 36 / 64, n = 4, 255 x 187 (1.7e8)
+// 78 / 104, 255 x 255 (2.7e8) 101 / 130, 401 x 401 (1.0e9) 264 / 233; single
 // dense products with walls, n = 3, 32 x 32 (1.8e6) 31 / 46, 128 x 128 (1.1e8)
 // 58 / 73, n = 4, 128 x 128 (2.7e8) 78 / 70: there the tiles of the library
 // fill the chip and reuse an operand more often.  Mixed-precision solves cross
@@ -276,10 +276,14 @@ int apply_fft(const FdDevice* fd, hipStream_t s) {
 // number of cells and one has more than 32 (each real row of N values is
 // transformed as a complex row of N/2), the folded GEMMs otherwise (the basis
 // with phases at the cell centres folds each axis to half size; an odd count
-// cannot be packed into half-length rows).  One FP64 apply with the FFTs
-// against the folded GEMMs: 41 / 60 us at n = 4, 64^2; 82 / 129 us at
-// n = 4, 256^2; 142 / 270 us at n = 4, 512^2; 210 / 401 us at n = 5, 512^2
-// (every order and size from 64 to 512 cells favours the FFTs).
+// cannot be packed into half-length rows).  One FP64 apply, FFTs / folded
+// products, us: n = 2, 34^2 36 / 28, 64^2 30 / 28, 128^2 32 / 31, 192^2 35 / 38,
+// 512^2 67 / 111; n = 3, 34^2 39 / 31, 64^2 32 / 31, 96^2 32 / 33, 256^2 54 / 72,
+// 512^2 101 / 220; n = 4, 34^2 44 / 36, 48^2 36 / 36, 128^2 39 / 44, 256^2 78 / 92,
+// 384^2 105 / 226; n = 5, 34^2 47 / 42, 48^2 40 / 42, 128^2 49 / 58, 256^2 101 /
+// 127, 384^2 128 / 247.  Both are equal within 7% from 48^2 to where the FFTs win
+// (n = 5 48, n = 4 64, n = 3 96, n = 2 192 cells); at 34 cells (a half length of 17)
+// the products are faster by up to 8 us.
 bool fd_uses_fft(int nx, int ny) {
     return (nx > kFdGemmMaxCells || ny > kFdGemmMaxCells) && nx % 2 == 0 && ny % 2 == 0;
 }

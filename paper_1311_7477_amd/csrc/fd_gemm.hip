@@ -7,8 +7,8 @@
 // chunk while this one is multiplied).  What bounds these sizes is the chain of
 // chunks -- load, store to LDS, fragments, products -- and how many CUs share
 // it, hence the small tiles and the long chunks: the whole inverse of n = 4,
-// 255 x 187 cells took 107 us with the library's products and takes 81, n = 3,
-// 127 x 127 66 and 36; with walls, n = 3, 128 x 128, 73 and 58.  Chunks of 32 in
+// 255 x 187 cells took 104 us with the library's products and takes 78, n = 3,
+// 127 x 127 64 and 36; with walls, n = 3, 128 x 128, 73 and 58.  Chunks of 32 in
 // two buffers measured the same, tiles of 64 x 32 were no faster at any size
 // that comes here, fragments read a group ahead were slower (86 us).
 #include <hip/hip_runtime.h>
