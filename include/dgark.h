@@ -196,9 +196,10 @@ int  dg_grid_tune(dg_grid* grid, const double* omega, int reps, double* ms_out5,
 
 /* ----------------------------------------------------------- workspace --- */
 /* Device bytes a workspace for (grid, mode) holds: CG vectors x, r, p, the
- * two RK stage fields (on a periodic grid without FP32 vectors or DG_WS_FD with
- * room for one more CG vector in place of one of them), reduction partials and scalars, plus FP32 r and p in
- * DG_PREC_MIXED mode, plus (DG_WS_FD) the preconditioner's z vector, two
+ * two RK stage fields (on a periodic grid without FP32 vectors with room for
+ * one more CG vector in place of one of them), reduction partials and
+ * scalars, plus FP32 r and p in DG_PREC_MIXED mode, plus (DG_WS_FD) the
+ * preconditioner's z vector, two
  * node-plane fields and per axis the factored eigenbasis in FP64 and FP32
  * (the N x N cell Fourier basis, 2 (N/2 + 1) mixing blocks of 2n x 2n and
  * n N eigenvalues; one set when the axes agree), a copy of omega and three

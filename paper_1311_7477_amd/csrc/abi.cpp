@@ -126,16 +126,15 @@ bool valid_mode(int mode) {
 }
 
 // The two RK stage fields.  The plain CG of a periodic grid needs one more L64 vector,
-// its second residual (second_residual): the vector of a preconditioned or of an
-// FP32-stored solve where the workspace has those, else the stage field that does not
-// hold its input, with room beside it for what an L64 vector is longer, shared by the
-// two: [s1 | ... | s2], the residual from the start or from the end of s1.
+// its second residual (second_residual): the vectors of an FP32-stored solve where the
+// workspace has those, else the stage field that does not hold its input, with room
+// beside it for what an L64 vector is longer, shared by the two: [s1 | ... | s2], the
+// residual from the start or from the end of s1.
 struct StageFields {
     size_t s2, total;      // offset of s2, and doubles in all
     StageFields(const dg_grid* g, int mode) {
         const size_t F = g->elems, L = l64_elems(g->geom);
-        const bool shared = !g->geom.bcx && !g->geom.bcy && !(mode & DG_WS_FD) &&
-                            prec_of(mode) != DG_PREC_MIXED;
+        const bool shared = !g->geom.bcx && !g->geom.bcy && prec_of(mode) != DG_PREC_MIXED;
         s2 = even(F) + (shared ? even(L - F) : 0);
         total = s2 + F;
     }
@@ -557,7 +556,6 @@ int periodic_only(const char* what) {
 }
 
 double* second_residual(const dg_workspace* ws, const double* input) {
-    if (ws->z) return ws->z;
     if (ws->r32) return reinterpret_cast<double*>(ws->r32);      // r32 and q0
     return input == ws->s1 ? ws->s1 + StageFields::even(ws->elems) : ws->s1;
 }
