@@ -12,13 +12,14 @@
 // the cells in its halos: bracket n = 5, 2048^2 806 -> 647 us (3.9 TB/s), n = 4,
 // 2048^2 456 -> 387, 1024^2 110 -> 101, n = 3, 2048^2 262 -> 195, n = 2, 2048^2 122
 // -> 88, n = 1, 2048^2 27 -> 19; with the viscous term and the stage combination
-// n = 5, 1024^2 317 -> 253.  What bounds it from n = 4 on are its vector
+// n = 5, 1024^2 317 -> 253.  What bounds it from n = 4 on is the chain of its vector
 // instructions (2550 a row of 62 cells at n = 5, 2400 of them FP64; 1400 at n = 4)
 // on one wave per SIMD: a cell's two fields, its sums, the traces and the row ahead
-// take 300 - 500 registers.  Counted at n = 5, 2048^2: a vector instruction in 54%
-// of a wave's cycles, most of the rest the latency between instructions that need
-// each other's results; 2.63 GB moved, 1.05 times the three fields.  A second wave hides little more: n = 4 without the row ahead fits two, 2048^2 387
-// -> 369 us, and then spills with the viscous term.
+// take 300 - 500 registers.  Counted at n = 5, 2048^2: one is issued in 54% of a
+// wave's cycles, most of the rest is the latency between those that need each
+// other's results; 2.63 GB moved, 1.05 times the three fields.  A second wave hides
+// little more: n = 4 without the row ahead fits two, 2048^2 387 -> 369 us, and then
+// spills with the viscous term.
 #include "dg_launch.h"
 #include "dg_stage.h"
 
