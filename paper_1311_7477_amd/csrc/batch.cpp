@@ -21,12 +21,15 @@ namespace {
 
 enum ListKind { kCell = 0, kStep, kRow, kPwRows, kPwCells, kPwElems, kListCount };
 
-// Launch groups: one per (polynomial order, cell tile height, CG tile height and
-// whether its rows wrap, bracket tile height); every kernel kind of a group is one fused launch.
+// Launch groups: one per (polynomial order, cell tile height, CG tile height,
+// bracket tile height); every kernel kind of a group is one fused launch.  Rows
+// that end within a wave are not a group apart: more groups than streams follow one
+// another (15 members of 56 to 68 cells, a step 77.0 ms; in one group with the
+// others of their order, in the kernel for both, 58.9).
 constexpr int kCellShapes[3] = {4, 8, 16};
 constexpr int kRowShapes[2] = {8, 16};
 constexpr int kStepShapes[2] = {4, 8};
-constexpr int kShapes = 24;
+constexpr int kShapes = 12;
 constexpr int kGroups = kMaxN * kShapes;
 using GroupMask = std::bitset<kGroups>;
 
@@ -37,19 +40,17 @@ int cell_shape(int waves) { return waves == 4 ? 0 : (waves == 8 ? 1 : 2); }
 
 int group_of(const Geom& g) {
     const int ri = g.rw == 8 ? 0 : 1;
-    const int si = (step_waves(g) == 4 ? 0 : 1) + (step_wraps(g) ? 2 : 0);
-    return (g.n - 1) * kShapes + (cell_shape(g.cw) * 4 + si) * 2 + ri;
+    const int si = step_waves(g) == 4 ? 0 : 1;
+    return (g.n - 1) * kShapes + (cell_shape(g.cw) * 2 + si) * 2 + ri;
 }
 
 struct GroupShape {
-    int n, cw, sw;
-    bool wrap;
-    int rw;
+    int n, cw, sw, rw;
 };
 
 GroupShape shape_of(int gi) {
     const int n = gi / kShapes + 1, s = gi % kShapes;
-    return GroupShape{n, kCellShapes[s / 8], kStepShapes[s / 2 % 2], s / 4 % 2 != 0, kRowShapes[s % 2]};
+    return GroupShape{n, kCellShapes[s / 4], kStepShapes[s / 2 % 2], kRowShapes[s % 2]};
 }
 
 struct Slot {
@@ -85,6 +86,7 @@ struct dg_batch {
     DevList lists[kGroups][kListCount];
     bool lists_dirty = true;
     GroupMask group_mask;          // bit gi set if some slot is in launch group gi
+    GroupMask wraps;               // ... whose rows of cells end within a wave (step_wraps)
     // CG chunks of different launch groups run on streams of their own (group
     // gi of a step takes lane rank(gi) mod kMaxLanes): groups share nothing, and
     // the iterations of a small group leave most of the chip idle
@@ -123,13 +125,14 @@ int grid_of(const dg_batch* b, int gi, int kind) {
 // upload them.
 int rebuild_lists(dg_batch* b, hipStream_t s) {
     std::vector<BatchItem> h[kGroups][kListCount];
-    GroupMask mask;
+    GroupMask mask, wraps;
     for (int i = 0; i < b->capacity; ++i) {
         const Slot& sl = b->slots[i];
         if (!sl.used) continue;
         const BatchInst& r = b->h_inst[i];
         const int gi = group_of(r.g);
         mask.set(gi);
+        if (step_wraps(r.g)) wraps.set(gi);
         // (members whose right-hand side goes by strips launch it alone)
         const int rows = rhs_strips(r.g) ? 0 : r.row_nblocks;
         const int counts[kListCount] = {r.cell_nblocks, r.step_nblocks, rows,
@@ -169,6 +172,7 @@ int rebuild_lists(dg_batch* b, hipStream_t s) {
     (void)realloc_any;
     destroy_graphs(b);
     b->group_mask = mask;
+    b->wraps = wraps;
     b->lists_dirty = false;
     return DG_OK;
 }
@@ -177,10 +181,10 @@ int enqueue_setup(dg_batch* b, hipStream_t s) {
     for (int gi = 0; gi < kGroups; ++gi) {
         if (!b->group_mask[gi]) continue;
         const GroupShape q = shape_of(gi);
-        hipError_t e = launch_batch(q.n, q.cw, q.sw, q.wrap, q.rw, BatchKernel::Mean, b->d_inst,
+        hipError_t e = launch_batch(q.n, q.cw, q.sw, b->wraps[gi], q.rw, BatchKernel::Mean, b->d_inst,
                                     list_of(b, gi, kPwRows), grid_of(b, gi, kPwRows), s);
         if (e == hipSuccess)
-            e = launch_batch(q.n, q.cw, q.sw, q.wrap, q.rw, BatchKernel::Init, b->d_inst,
+            e = launch_batch(q.n, q.cw, q.sw, b->wraps[gi], q.rw, BatchKernel::Init, b->d_inst,
                              list_of(b, gi, kCell), grid_of(b, gi, kCell), s);
         if (e != hipSuccess) return hip_fail(e, "batch setup launch");
     }
@@ -193,7 +197,7 @@ int enqueue_setup(dg_batch* b, hipStream_t s) {
 int enqueue_chunk(dg_batch* b, int gi, hipStream_t s) {
     const GroupShape q = shape_of(gi);
     for (int i = 0; i < b->chunk; ++i) {
-        hipError_t e = launch_batch(q.n, q.cw, q.sw, q.wrap, q.rw,
+        hipError_t e = launch_batch(q.n, q.cw, q.sw, b->wraps[gi], q.rw,
                                     i & 1 ? BatchKernel::StepOdd : BatchKernel::StepEven,
                                     b->d_inst, list_of(b, gi, kStep), grid_of(b, gi, kStep), s);
         if (e != hipSuccess) return hip_fail(e, "batch CG launch");
@@ -205,13 +209,13 @@ int enqueue_finish(dg_batch* b, hipStream_t s) {
     for (int gi = 0; gi < kGroups; ++gi) {
         if (!b->group_mask[gi]) continue;
         const GroupShape q = shape_of(gi);
-        hipError_t e = launch_batch(q.n, q.cw, q.sw, q.wrap, q.rw, BatchKernel::Finish, b->d_inst,
+        hipError_t e = launch_batch(q.n, q.cw, q.sw, b->wraps[gi], q.rw, BatchKernel::Finish, b->d_inst,
                                     list_of(b, gi, kPwCells), grid_of(b, gi, kPwCells), s);
         if (e == hipSuccess)
-            e = launch_batch(q.n, q.cw, q.sw, q.wrap, q.rw, BatchKernel::SubMean, b->d_inst,
+            e = launch_batch(q.n, q.cw, q.sw, b->wraps[gi], q.rw, BatchKernel::SubMean, b->d_inst,
                              list_of(b, gi, kPwElems), grid_of(b, gi, kPwElems), s);
         if (e == hipSuccess)
-            e = launch_batch(q.n, q.cw, q.sw, q.wrap, q.rw, BatchKernel::Rhs, b->d_inst,
+            e = launch_batch(q.n, q.cw, q.sw, b->wraps[gi], q.rw, BatchKernel::Rhs, b->d_inst,
                              list_of(b, gi, kRow), grid_of(b, gi, kRow), s);
         if (e != hipSuccess) return hip_fail(e, "batch finish launch");
     }

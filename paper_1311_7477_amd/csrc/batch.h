@@ -52,7 +52,7 @@ enum class BatchKernel { Mean, Init, StepEven, StepOdd, Finish, SubMean, Rhs };
 void fill_batch_geometry(BatchInst& b);
 // One fused launch of `kind` for polynomial order n with cell tiles of
 // cw waves (Init) or sw waves (Step*: one CG iteration of that parity; wrap: rows that
-// end within a wave) and bracket tiles of rw waves (Rhs).
+// end within a wave are among the items) and bracket tiles of rw waves (Rhs).
 hipError_t launch_batch(int n, int cw, int sw, bool wrap, int rw, BatchKernel kind, const BatchInst* inst,
                         const ItemList& list, int grid, hipStream_t s);
 

@@ -157,8 +157,8 @@ __device__ __forceinline__ void add_to_x(double* __restrict__ x, const double* p
     }
 }
 
-// kWrap: rows of 61 to 63 cells, which end within the wave (a template parameter:
-// tested for at run time, all other rows take 8 to 30% longer at n = 5).
+// kWrap: there may be rows of 61 to 63 cells, which end within the wave (a template
+// parameter: compiled in, other rows take 8 to 30% longer at n = 5).
 // par: the launch's parity, that of the iteration while the solve runs.  The
 // scalars and block sums written by the launch before are read from sc_in and
 // part_in, this launch's go to sc_out and part_out.
@@ -173,7 +173,7 @@ __device__ __forceinline__ void cg_step_body(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int t = xcd_tile(b, nblocks);
     const int ty = t / tilesX, tx = t - ty * tilesX;
-    const int rim = kWrap ? 0 : step_rim(g);
+    const int rim = step_rim(g);
     const int cx = tx * (64 - 2 * rim) + lane - rim, cy = ty * (WV - 2) + wave - 1;
     const bool inner = wave > 0 && wave < WV - 1 && cy < g.ny;        // wave-uniform
     const bool store = inner && lane >= rim && lane < 64 - rim && cx < g.nx;
@@ -272,6 +272,7 @@ __device__ __forceinline__ void cg_step_body(
     beta = read_lane(beta, 0);
     const double ax = read_lane(s.alpha, 0), ax_prev = read_lane(s.alpha_prev, 0);
 
+    const int end = step_wraps(g) ? g.nx - 1 : 64, start = step_wraps(g) ? 0 : 64;
     double fR[N], fL[N];
     // this cell's face scalars to the neighbouring waves and lanes
     auto publish = [&](const double (&u)[N * N]) {
@@ -286,9 +287,9 @@ __device__ __forceinline__ void cg_step_body(
             fR[j] = lane_next(toL);
             fL[j] = lane_prev(toR);
             if (kWrap) {
-                const double first = read_lane(toL, 0), last = read_lane(toR, g.nx - 1);
-                if (lane == g.nx - 1) fR[j] = first;
-                if (lane == 0) fL[j] = last;
+                const double first = read_lane(toL, 0), last = read_lane(toR, end & 63);
+                if (lane == end) fR[j] = first;
+                if (lane == start) fL[j] = last;
             }
         }
     };

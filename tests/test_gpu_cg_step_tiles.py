@@ -59,3 +59,25 @@ def test_batch_members():
         dg.rk_step(grid, w0, st, dg.Workspace(grid), dt, D, opts)
         assert torch.equal(w, w0)
         assert torch.equal(batch.psi(slot), st.psi())
+
+
+# members whose rows end within a wave in one launch group with others
+def test_batch_group_of_both():
+    from paper_1311_7477_amd import dg
+    print("cg step tiles batch, one group", flush=True)
+    opts, dt, D = dg.cg_opts(rtol=1e-9), 1e-4, 1e-4
+    batch, inst = dg.Batch(9), []
+    for n, nx, ny in ((2, 61, 9), (2, 33, 30), (3, 62, 18), (3, 64, 17), (3, 60, 20), (3, 130, 5),
+                      (4, 63, 7), (5, 1, 40), (5, 63, 12)):
+        grid = dg.Grid(n, nx, ny)
+        w0 = torch.from_numpy(I.random_modes(n, nx, ny, seed=nx)).cuda()
+        w = w0.clone()
+        inst.append((batch.attach(grid, w, dt, D), grid, w0, w))
+    for _ in range(2):
+        assert batch.rk_step(opts)[1]
+    for slot, grid, w0, w in inst:
+        st, ws = dg.State(grid), dg.Workspace(grid)
+        for _ in range(2):
+            dg.rk_step(grid, w0, st, ws, dt, D, opts)
+        assert torch.equal(w, w0)
+        assert torch.equal(batch.psi(slot), st.psi())
